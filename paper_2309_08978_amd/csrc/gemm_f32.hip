@@ -332,7 +332,7 @@ static hipError_t launch_gemm_f32(const void *params, dim3 grid, hipStream_t str
 // which the two half-waves read in the same instruction, sit on opposite
 // halves of the 64 banks.  Lane group g (l / 32) takes k in [8g, 8g + 8) of
 // a slab, as in the kernel above.
-template <int MT, int NT, int KS, int ST>
+template <int MT, int NT, int KS, int ST, bool SP = false>
 __global__ void __launch_bounds__(KS * 64)
 gemm_f32w_kernel(GemmParams p)
 {
@@ -482,10 +482,52 @@ gemm_f32w_kernel(GemmParams p)
                 for (int j = 0; j < FN; ++j) acc[i][j] = I::mma(a[i][t], b[t][j], acc[i][j]);
     };
 
+    // SP: the same fragments in three bf16 parts.  A slab's eight k of a lane
+    // are what the 32x32x16 instruction takes, so the layouts above serve
+    // both; a wave's operands are its own, so each is split once.
+    unsigned tiny = kTinyStart;   // the smallest operand this lane split
+    auto read_split = [&](int st, Split8 (&a)[FM], Split8 (&b)[FN]) {
+        f32x8 fa[FM];
+        float fb[8][FN];
+        read_frags(st, fa, fb);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) a[i] = split8(fa[i], tiny);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            f32x8 v;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = fb[t][j];
+            b[j] = split8(v, tiny);
+        }
+    };
+    auto mma_split = [&](const Split8 (&a)[FM], const Split8 (&b)[FN]) {
+        auto one = [&](auto pa, auto pb) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = mma_bf16(pa(a[i]), pb(b[j]), acc[i][j]);
+        };
+        auto H = [](const Split8 &x) { return x.h; };
+        auto Mi = [](const Split8 &x) { return x.m; };
+        auto L = [](const Split8 &x) { return x.l; };
+        one(H, L);
+        one(L, H);
+        one(Mi, Mi);
+        one(H, Mi);
+        one(Mi, H);
+        one(H, H);
+    };
+
     // one slab: every fragment read is issued before the first MFMA (the
     // reads return in order, so MFMA t waits only for the reads it uses and
     // the LDS latency is paid once per slab rather than once per step)
     auto compute = [&](int st) {
+        if constexpr (SP) {
+            Split8 a[FM], b[FN];
+            read_split(st, a, b);
+            mma_split(a, b);
+            return;
+        }
         f32x8 a[FM];
         float b[8][FN];
         read_frags(st, a, b);
@@ -502,7 +544,25 @@ gemm_f32w_kernel(GemmParams p)
     // rest runs with checked copies and a guard per slab.  Both issue NCOPY
     // copies per iteration, so the counted waits are the same.
     int it0 = 0;
-    if constexpr (ST >= 4 && FM * FN >= 2) {
+    if constexpr (SP) {
+        static_assert(ST == 4, "the two register sets alternate within a group of ST slabs");
+        // as below, with slab it + 1 split while the MFMAs of slab it run
+        if (2 * ST - 1 <= nfull_mine) {
+            Split8 fa[2][FM], fb[2][FN];
+            wait_vmcnt<(ST - 2) * NCOPY>();   // slab 0
+            read_split(0, fa[0], fb[0]);
+            for (; it0 + 2 * ST - 1 <= nfull_mine; it0 += ST) {
+#pragma unroll
+                for (int u = 0; u < ST; ++u) {
+                    wait_vmcnt<(ST - 3) * NCOPY>();
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    copy_full((u + ST - 1) % ST, it0 + u + ST - 1);
+                    read_split((u + 1) % ST, fa[(u + 1) & 1], fb[(u + 1) & 1]);
+                    mma_split(fa[u & 1], fb[u & 1]);
+                }
+            }
+        }
+    } else if constexpr (ST >= 4 && FM * FN >= 2) {
         static_assert(ST % 2 == 0, "the two register sets alternate within a group of ST slabs");
         // with four or more stages and at least two accumulator tiles (a
         // slab of >= 16 MFMAs, long enough to cover a copy with one fewer
@@ -561,6 +621,48 @@ gemm_f32w_kernel(GemmParams p)
         }
     }
     wait_vmcnt<0>();   // no copy may still target LDS when the region is reused
+
+    if constexpr (SP) {
+        // sums that the split does not serve are taken anew in fp32 over this
+        // wave's slabs (kcommon.h)
+        float probe = 0.f, least = kTinySum;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < I::NR; ++r) {
+                    probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
+                    least = fminf(least, fabsf(acc[i][j][r]));
+                }
+        if (__any(!(probe == 0.f)) || (__any(tiny < kTinyLimit) && __any(least < kTinySum))) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int r = 0; r < I::NR; ++r) acc[i][j][r] = 0.f;
+#pragma unroll 1
+            for (int t = 0; t < nmine * (KT / 2); ++t) {
+                const int gk = kbeg + (wave_u + (t / (KT / 2)) * KS) * KT + 2 * (t % (KT / 2)) + lg;
+                float a[FM], b[FN];
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+                    const int gm = m0 + 32 * i + li;
+                    a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
+                }
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const int gn = n0 + 32 * j + li;
+                    b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
+                }
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) acc[i][j] = I::mma(a[i], b[j], acc[i][j]);
+            }
+        }
+    }
     __syncthreads();
 
     // every wave's partial tile to LDS, then wave w adds register slots
@@ -621,10 +723,10 @@ gemm_f32w_kernel(GemmParams p)
     }
 }
 
-template <int MT, int NT, int KS, int ST>
+template <int MT, int NT, int KS, int ST, bool SP = false>
 static hipError_t launch_gemm_f32w(const void *params, dim3 grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((gemm_f32w_kernel<MT, NT, KS, ST>), grid, dim3(KS * 64), 0, stream, *(const GemmParams *)params);
+    hipLaunchKernelGGL((gemm_f32w_kernel<MT, NT, KS, ST, SP>), grid, dim3(KS * 64), 0, stream, *(const GemmParams *)params);
     return hipGetLastError();
 }
 
@@ -1024,6 +1126,25 @@ constexpr int lds_f32w(int mt, int nt, int ks, int st) {
     X(128, 32, 4, 3) \
     X(32, 128, 4, 3)
 
+// The same on the bf16 matrix cores, operands split in three (kcommon.h).  A
+// slab of a 64 x 64 tile takes 24 MFMAs of 32 cycles instead of 32 of 64, and
+// 176 VALU instructions to split that run beside them: 1024 x 1024 x 1024
+// 22.1 -> 18.0 us, 256 x 4096 x 4096 69 -> 54 us, 128 x 2304 x 768 (64 x 32)
+// 10.7 -> 9.9 us.  On 32 x 32 tiles the split costs as much as the MFMAs save
+// (64 x 768 x 768: 7.3 -> 7.6 us), so they are not compiled.
+#define NNJIT_F32WS_VARIANT(MT, NT, KS, ST)                                                                   \
+    {"gemm_f32ws_" #MT "x" #NT "x16_k" #KS "_s" #ST, FAM_GEMM_F32, 32, 16, MT, NT, 16, 1, 1, ST, ST - 1, KS, 16, \
+     0, 0, KS * 64, lds_f32w(MT, NT, KS, ST), est_regs_f32w(MT, NT) + 24 * (MT / 32 + NT / 32),               \
+     (const void *)&gemm_f32w_kernel<MT, NT, KS, ST, true>, &launch_gemm_f32w<MT, NT, KS, ST, true>, 2, LAYOUT_SWIZZLE, 0}
+
+#define NNJIT_F32WS_LIST(X) \
+    X(64, 32, 4, 4) \
+    X(32, 64, 4, 4) \
+    X(64, 64, 4, 4)
+
+#define NNJIT_F32WS_INST(MT, NT, KS, ST) template __global__ void gemm_f32w_kernel<MT, NT, KS, ST, true>(GemmParams);
+NNJIT_F32WS_LIST(NNJIT_F32WS_INST)
+
 #define NNJIT_F32W_INST(MT, NT, KS, ST) template __global__ void gemm_f32w_kernel<MT, NT, KS, ST>(GemmParams);
 NNJIT_F32W_LIST(NNJIT_F32W_INST)
 
@@ -1152,9 +1273,11 @@ NNJIT_F32P_LIST(NNJIT_F32P_INST)
 #if !defined(__HIP_DEVICE_COMPILE__)
 #define NNJIT_F32_ENTRY(...) NNJIT_F32_VARIANT(__VA_ARGS__),
 #define NNJIT_F32W_ENTRY(...) NNJIT_F32W_VARIANT(__VA_ARGS__),
+#define NNJIT_F32WS_ENTRY(...) NNJIT_F32WS_VARIANT(__VA_ARGS__),
 #define NNJIT_F32T_ENTRY(...) NNJIT_F32T_VARIANT(__VA_ARGS__),
 #define NNJIT_F32P_ENTRY(...) NNJIT_F32P_VARIANT(__VA_ARGS__),
 const Variant kGemmF32Variants[] = {NNJIT_F32_LIST(NNJIT_F32_ENTRY) NNJIT_F32W_LIST(NNJIT_F32W_ENTRY)
+                                        NNJIT_F32WS_LIST(NNJIT_F32WS_ENTRY)
                                         NNJIT_F32T_LIST(NNJIT_F32T_ENTRY) NNJIT_F32P_LIST(NNJIT_F32P_ENTRY)};
 const int kNumGemmF32Variants = sizeof(kGemmF32Variants) / sizeof(kGemmF32Variants[0]);
 #endif

@@ -1,0 +1,421 @@
+// fp32 MatMul / BatchMatMul on the bf16 matrix cores ("gemm_f32s"), the
+// operands split in three bf16 parts (see split8 in kcommon.h).
+//
+// Why: the fp32 matrix-core instructions run at 157 TFLOP/s dense and the
+// fp32 kernels were at 82-90% of that; six bf16 products per fp32 product run
+// at up to 2517 / 6 = 419 TFLOP/s.  The sums are no less accurate: against
+// fp64 the relative error (2-norm) of 512 x 32000 x 4096 is 1.0e-6 where the
+// fp32 instructions give 1.1e-6, of 1024 x 4096 x 1024 4.9e-7 against 5.7e-7,
+// of 256 x 256 x 64 1.1e-7 against 1.4e-7 (16 terms are summed per rounding
+// instead of two).
+//
+// One workgroup computes an Mt x Nt tile for one split of K and one batch
+// slice.  Each operand element is loaded into registers once per workgroup,
+// split there and stored to LDS as three bf16 planes, so the split costs
+// (Mt + Nt) / (Mt Nt) of what splitting each wave's fragments would (that
+// form, with fp32 slabs copied straight to LDS, measured the same on 512 x
+// 32000 x 4096 but 2-4% slower from 1024 x 4096 x 1024 down).  Three LDS
+// stages: slab k is multiplied, k + 1 is visible, k + 2 is being stored, and
+// PF more slabs are on their way in registers; one barrier per slab.
+//   A plane [Mt rows][Kt halves], 16-byte chunk c of row r at c ^ ((r >> 3) & 1)
+//     (Kt = 16) or c ^ ((r >> 2) & 3) (Kt = 32): 16 rows read at one chunk
+//     cover the 64 banks once;
+//   B plane [Kt k rows][Nt halves] read through ds_read_b64_tr_b16, as in
+//     gemm_f16t: the 32-byte unit u of row k at u ^ b_swz(k).
+// SQ_LDS_BANK_CONFLICT is 0.
+//
+// Measured (random operands, one MI355X): 512 x 32000 x 4096, 256 x 256 tiles:
+// 947 -> 637-663 us (142 -> 202-210 TFLOP/s, 1.26 PFLOP/s of bf16 products);
+// 1024 x 4096 x 1024, 128 x 128 tiles: 67 -> 50-52 us; 512 x 4096 x 11008:
+// 335 -> 230 us.  The large tiles run at the power limit: on zero operands the
+// first takes 509 us.  Eight waves beat four (one per SIMD) except where LDS
+// holds several workgroups.
+//
+// VEC false: operands of any alignment.  gfx950 loads 16 bytes at any element
+// address, so the same 128-bit loads serve; only a slab that reaches past the
+// K range or behind the last rows of B takes element loads.
+#include "kcommon.h"
+
+namespace nnjit {
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>
+__global__ void __launch_bounds__(WM * WN * 64)
+gemm_f32s_kernel(GemmParams p)
+{
+    typedef f32x16 acc_t;
+    constexpr int ST = 3;
+    constexpr int NTHR = WM * WN * 64;
+    constexpr int WTM = MT / WM, WTN = NT / WN;
+    constexpr int FM = WTM / 32, FN = WTN / 32;
+    constexpr int ACH = KT / 8;                      // 8-element units per A row of a slab
+    constexpr int AU = MT * ACH, BU = KT * NT / 8;   // units of one slab
+    constexpr int NU = AU + BU;
+    constexpr int LU = (NU + NTHR - 1) / NTHR;       // units per thread
+    constexpr int APL = AU * 16, BPL = BU * 16;      // bytes of one bf16 plane
+    constexpr int STAGE = 3 * (APL + BPL);
+    constexpr int NSTEP = KT / 16;                   // matrix-core K steps per slab
+    static_assert(KT == 16 || KT == 32, "K slab");
+    static_assert(AU % 64 == 0 && BU % 64 == 0, "a wave's units are of one operand");
+    static_assert(NT >= 64 && (NT & (NT - 1)) == 0, "B rows of a power of two >= 64");
+    static_assert(PF == 1 || PF == ST, "staging sets");
+    static_assert(FM >= 1 && FN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
+
+    __shared__ __attribute__((aligned(1024))) char smem[ST * STAGE];
+    typedef __attribute__((address_space(3))) char lds_char;
+
+    const int tiles = p.tiles_m * p.tiles_n;
+    const int gx = gridDim.x;
+    const int logical = xcd_remap(blockIdx.x + gx * blockIdx.z, gx * gridDim.z);
+    const int M = p.M, N = p.N;
+    const long long lda = p.lda, ldb = p.ldb;
+    const float *zero = (const float *)p.zero;
+
+    auto a_swz = [](int row) { return KT == 16 ? ((row >> 3) & 1) : ((row >> 2) & 3); };
+    auto b_swz = [](int k) { return NT >= 128 ? (((k & 3) << 1) | ((k >> 3) & 1)) : (((k >> 1) & 1) << 1); };
+
+    const int z = logical / gx;
+    const int rest = logical - z * gx;
+    const int s = rest / tiles;
+    const int tile = rest - s * tiles;
+    const int kbeg = s * p.kchunk;
+    const int kend = min(p.K, kbeg + p.kchunk);
+    int tm, tn;
+    tile_of(tile, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    const int m0 = tm * MT, n0 = tn * NT;
+    const int nk = kend > kbeg ? (kend - kbeg + KT - 1) / KT : 0;
+    const float *A = (const float *)p.A + (long long)z * p.sA;
+    const float *B = (const float *)p.B + (long long)z * p.sB;
+    float *C = p.C + (long long)z * p.sC;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int li = lane & 31, lg = lane >> 5;
+    // unit u of this wave: of A, of B, or none (the last round may be short)
+    auto unit_of_a = [&](int u) { return wave_u * 64 + u * NTHR < AU; };
+    auto unit_live = [&](int u) { return NU % NTHR == 0 || u + 1 < LU || wave_u * 64 + u * NTHR < NU; };
+
+    // This thread's units: 8 consecutive k of an A row, or 8 consecutive
+    // columns of a B row (which of the two is the same for a whole wave).
+    // Rows past M and units past N point at row / column 0: what they bring
+    // reaches only outputs that are never stored.
+    const float *u_src[LU];
+    int u_dst[LU];
+#pragma unroll
+    for (int u = 0; u < LU; ++u) {
+        const int f = tid + u * NTHR;
+        if (unit_of_a(u)) {
+            const int row = f / ACH, c = f % ACH;
+            u_src[u] = A + (long long)(m0 + row < M ? m0 + row : 0) * lda + kbeg + 8 * c;
+            u_dst[u] = row * (KT * 2) + 16 * (c ^ a_swz(row));
+        } else {
+            const int g = f - AU;
+            const int k = g / (NT / 8), c = g % (NT / 8);
+            u_src[u] = B + (long long)(kbeg + k) * ldb + (n0 + 8 * c < N ? n0 + 8 * c : 0);
+            u_dst[u] = 3 * APL + k * (NT * 2) + 32 * ((c >> 1) ^ b_swz(k)) + 16 * (c & 1);
+        }
+    }
+    // Whole slabs whose units can be read without checks: a B unit that
+    // begins before column N and ends after it runs on into the next row,
+    // which lies inside the operand except behind its last rows.
+    int safe_k = kend;
+    if ((N & 7) != 0) safe_k = min(kend, p.K - (ldb >= 7 ? 1 : 7));
+    const int nfull = safe_k > kbeg ? (safe_k - kbeg) / KT : 0;
+
+    // The 128-row wave tile has no register to spare for the addresses of each
+    // stage: its stage offset goes through an opaque scalar, so that they are
+    // formed where they are used.
+    auto stage_base = [&](int stage) -> lds_char * {
+        unsigned off = stage * STAGE;
+        if constexpr (FM >= 4) asm volatile("" : "+s"(off));
+        return (lds_char *)smem + off;
+    };
+
+    f32x4 st[PF][LU][2];
+    unsigned tiny = kTinyStart;   // the smallest operand this thread split
+    auto load_full = [&](int set, int kk) {
+#pragma unroll
+        for (int u = 0; u < LU; ++u) {
+            if (!unit_live(u)) continue;
+            const bool is_a = unit_of_a(u);
+            const float *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
+            if constexpr (VEC) {
+                st[set][u][0] = *(const f32x4 *)src;
+                st[set][u][1] = *(const f32x4 *)(src + 4);
+            } else {
+                st[set][u][0] = *(const f32x4u *)src;
+                st[set][u][1] = *(const f32x4u *)(src + 4);
+            }
+        }
+    };
+    // a slab that reaches past the K range or the last column: elements out
+    // of range are read from the zero buffer (only the address is selected)
+    auto load_checked = [&](int set, int kk) {
+        // indices taken afresh from an opaque copy of the thread id, so that
+        // they are not held in registers across the loop over the slabs
+        int t = tid;
+        asm volatile("v_mov_b32 %0, %0" : "+v"(t));
+#pragma unroll
+        for (int u = 0; u < LU; ++u) {
+            if (!unit_live(u)) continue;
+            const int f = t + u * NTHR;
+            const bool is_a = unit_of_a(u);
+            const float *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
+            int have;   // elements of the unit in range
+            if (is_a) {
+                have = kend - (kbeg + kk * KT + 8 * (f % ACH));
+            } else {
+                const int g = f - AU;
+                const int n = n0 + 8 * (g % (NT / 8));
+                have = kbeg + kk * KT + g / (NT / 8) < kend ? (n < N ? N - n : 8) : 0;
+                if (n >= N && N < 8) have = min(have, N);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; e += 4) {
+                if constexpr (VEC) {
+                    st[set][u][e / 4] = *(const f32x4 *)(e < have ? src + e : zero);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) st[set][u][e / 4][q] = *(e + q < have ? src + e + q : zero);
+                }
+            }
+        }
+    };
+    auto load_slab = [&](int set, int kk) {
+        if (kk < nfull) load_full(set, kk);
+        else if (kk < nk) load_checked(set, kk);
+    };
+    auto store_slab = [&](int set, int stage) {
+        lds_char *base = stage_base(stage);
+#pragma unroll
+        for (int u = 0; u < LU; ++u) {
+            if (!unit_live(u)) continue;
+            const int pl = unit_of_a(u) ? APL : BPL;
+            const Split8 v = split8(__builtin_shufflevector(st[set][u][0], st[set][u][1], 0, 1, 2, 3, 4, 5, 6, 7), tiny);
+            lds_char *d = base + u_dst[u];
+            *(lds_u32x4 *)d = __builtin_bit_cast(u32x4, v.h);
+            *(lds_u32x4 *)(d + pl) = __builtin_bit_cast(u32x4, v.m);
+            *(lds_u32x4 *)(d + 2 * pl) = __builtin_bit_cast(u32x4, v.l);
+        }
+    };
+
+    acc_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    const int grp = lane >> 4, tr_r = (lane >> 2) & 3, tr_q = lane & 3;
+    const int tr_n = 16 * (grp & 1) + 4 * tr_q;
+    auto read_a = [&](int stage, int step, int i) -> Split8 {
+        const int row = wm * WTM + 32 * i + li;
+        lds_char *a = stage_base(stage) + row * (KT * 2) + 16 * ((2 * step + lg) ^ a_swz(row));
+        return Split8{__builtin_bit_cast(bf16x8, *(lds_u32x4 *)a), __builtin_bit_cast(bf16x8, *(lds_u32x4 *)(a + APL)),
+                      __builtin_bit_cast(bf16x8, *(lds_u32x4 *)(a + 2 * APL))};
+    };
+    auto read_b = [&](int stage, int step, int j, int pl) -> bf16x8 {
+        const int n = wn * WTN + 32 * j + tr_n;
+        s16x4 h[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            const int k = 16 * step + 8 * (grp >> 1) + 4 * hh + tr_r;
+            lds_char *b = stage_base(stage) + 3 * APL + pl * BPL + k * (NT * 2) +
+                          32 * ((n >> 4) ^ b_swz(k)) + 2 * (n & 15);
+            h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)b);
+        }
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // fragments of B of one K step: part 0 .. 2 = h, m, l
+    bf16x8 b[3][FN];
+    auto mma_part = [&](int i, const bf16x8 &x, int part) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = mma_bf16(x, b[part][j], acc[i][j]);
+    };
+
+    if (nk > 0) {
+        // slabs 0 and 1 into LDS, slabs 2 .. PF + 1 on their way
+        if constexpr (PF == 1) {
+            load_slab(0, 0);
+            store_slab(0, 0);
+            load_slab(0, 1);
+            store_slab(0, 1);
+            load_slab(0, 2);
+        } else {
+            load_slab(0, 0);
+            load_slab(1, 1);
+            load_slab(2, 2);
+            store_slab(0, 0);
+            load_slab(0, 3);
+            store_slab(1, 1);
+            load_slab(1, 4);
+        }
+        lds_barrier();
+        Split8 a = read_a(0, 0, 0);
+        auto read_b_part = [&](int stage, int step, int part) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) b[part][j] = read_b(stage, step, j, part);
+        };
+        for (int part = 2; part >= 0; --part) read_b_part(0, 0, part);
+        // the products of the slab in stage u.  The next row's A fragments are
+        // read while this row's products run; the last row reads the next
+        // step's (or the next slab's) first ones, and each part of B again as
+        // soon as its last product is issued (so B needs one register set).
+        auto compute = [&](int u) {
+#pragma unroll
+            for (int q = 0; q < NSTEP; ++q)
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+                    const bool last_row = i + 1 == FM, last = last_row && q + 1 == NSTEP;
+                    const int stage = last ? (u + 1) % ST : u, step = last_row ? (q + 1) % NSTEP : q;
+                    const Split8 an = read_a(stage, step, last_row ? 0 : i + 1);
+                    mma_part(i, a.h, 2);
+                    if (last_row) read_b_part(stage, step, 2);
+                    mma_part(i, a.h, 1);
+                    mma_part(i, a.m, 1);
+                    if (last_row) read_b_part(stage, step, 1);
+                    mma_part(i, a.l, 0);
+                    mma_part(i, a.m, 0);
+                    mma_part(i, a.h, 0);
+                    if (last_row) read_b_part(stage, step, 0);
+                    a = an;
+                    // keep the 128-row wave tile within its registers: no
+                    // fragment read is moved up past a row of products
+                    if constexpr (FM >= 4) __builtin_amdgcn_sched_barrier(0);
+                }
+        };
+        int it0 = 0;
+        // while every slab loaded is whole: one branch-free block per slab
+        for (; it0 + ST + 2 + PF <= nfull; it0 += ST) {
+#pragma unroll
+            for (int u = 0; u < ST; ++u) {
+                const int set = PF == 1 ? 0 : (u + 2) % ST;
+                store_slab(set, (u + 2) % ST);
+                load_full(set, it0 + u + 2 + PF);
+                compute(u);
+                lds_barrier();
+            }
+        }
+        for (; it0 < nk; it0 += ST) {
+#pragma unroll
+            for (int u = 0; u < ST; ++u) {
+                const int set = PF == 1 ? 0 : (u + 2) % ST;
+                store_slab(set, (u + 2) % ST);
+                load_slab(set, it0 + u + 2 + PF);
+                if (it0 + u < nk) compute(u);
+                lds_barrier();
+            }
+        }
+    }
+
+    const int rwave = wm * WTM, cwave = wn * WTN + li;
+    auto row_of = [&](int r) { return 8 * (r >> 2) + 4 * lg + (r & 3); };
+
+    // sums that the split does not serve are taken anew in fp32 (kcommon.h):
+    // not finite ones by the wave that holds them, and all of the workgroup's
+    // if it split a tiny operand and holds a tiny sum
+    float probe = 0.f, least = kTinySum;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
+                least = fminf(least, fabsf(acc[i][j][r]));
+            }
+    bool anew = __any(!(probe == 0.f));
+    if (__syncthreads_or(tiny < kTinyLimit)) anew = anew || __any(least < kTinySum);
+    if (anew) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll 2
+        for (int k = kbeg; k < kend; k += 2) {
+            const int gk = k + lg;
+            float a[FM], b[FN];
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                const int gm = m0 + rwave + 32 * i + li;
+                a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int gn = n0 + cwave + 32 * j;
+                b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
+            }
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    }
+
+    float *out = C + (long long)m0 * p.ldc + n0;
+    long long ldo = p.ldc;
+    const int rows = M - m0, cols = N - n0;
+    if (p.S > 1) {
+        out = p.ws + (((long long)s * p.batch + z) * (long long)M + m0) * N + n0;
+        ldo = N;
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = rwave + 32 * i + row_of(r), col = cwave + 32 * j;
+                if (row < rows && col < cols) out[(long long)row * ldo + col] = acc[i][j][r];
+            }
+}
+
+template <int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>
+static hipError_t launch_gemm_f32s(const void *params, dim3 grid, hipStream_t stream)
+{
+    hipLaunchKernelGGL((gemm_f32s_kernel<MT, NT, KT, WM, WN, PF, VEC>), grid, dim3(WM * WN * 64), 0, stream,
+                       *(const GemmParams *)params);
+    return hipGetLastError();
+}
+
+// accumulators, two A and two sets of B fragments (12 registers each), the
+// staging registers and a fixed overhead
+constexpr int est_regs_f32s(int mt, int nt, int kt, int wm, int wn, int pf) {
+    return (mt / wm) * (nt / wn) / 64 + 24 * (1 + (nt / wn) / 32) + (pf + 1) * (mt + nt) * kt / (wm * wn * 64) + 32;
+}
+// three stages of three planes, and the flag of the workgroup-wide test
+constexpr int lds_f32s(int mt, int nt, int kt) { return 18 * kt * (mt + nt) + 256; }
+#define NNJIT_F32S_VARIANT(MT, NT, KT, WM, WN, PF, VEC)                                                       \
+    {"gemm_f32s_" #MT "x" #NT "x" #KT "_w" #WM "x" #WN "_p" #PF "_v" #VEC, FAM_GEMM_F32, 32, 16, MT, NT, KT, WM, WN, 3, PF, \
+     1, (VEC ? 16 : 4), 0, 0, WM * WN * 64, lds_f32s(MT, NT, KT), est_regs_f32s(MT, NT, KT, WM, WN, PF),      \
+     (const void *)&gemm_f32s_kernel<MT, NT, KT, WM, WN, PF, VEC>, &launch_gemm_f32s<MT, NT, KT, WM, WN, PF, VEC>, 2, LAYOUT_SWIZZLE, 0}
+
+#define NNJIT_F32S_LIST(X) \
+    X(256, 256, 16, 2, 4, 1, true) \
+    X(256, 128, 16, 4, 2, 3, true) \
+    X(128, 256, 16, 2, 4, 3, true) \
+    X(128, 128, 16, 2, 4, 3, true) \
+    X(64, 64, 16, 2, 2, 3, true) \
+    X(128, 128, 16, 2, 4, 3, false) \
+    X(64, 64, 16, 2, 2, 3, false)
+
+#define NNJIT_F32S_INST(MT, NT, KT, WM, WN, PF, VEC) \
+    template __global__ void gemm_f32s_kernel<MT, NT, KT, WM, WN, PF, VEC>(GemmParams);
+NNJIT_F32S_LIST(NNJIT_F32S_INST)
+
+#if !defined(__HIP_DEVICE_COMPILE__)
+#define NNJIT_F32S_ENTRY(...) NNJIT_F32S_VARIANT(__VA_ARGS__),
+const Variant kGemmF32sVariants[] = {NNJIT_F32S_LIST(NNJIT_F32S_ENTRY)};
+const int kNumGemmF32sVariants = sizeof(kGemmF32sVariants) / sizeof(kGemmF32sVariants[0]);
+#endif
+
+}  // namespace nnjit

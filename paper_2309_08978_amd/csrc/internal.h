@@ -85,7 +85,8 @@ struct Variant {
     int est_regs;         // VGPR+AGPR estimate per lane (the Table 1 register formula)
     const void *kernel;   // device function (attribute queries)
     LaunchFn launch;
-    int direct_copy;      // 1: slabs go global -> LDS by direct copies (staging in LDS, not registers)
+    int direct_copy;      // 0: slabs staged through registers; 1: global -> LDS by direct copies (staging in
+                          // LDS, not registers); 2: fp32 products on the bf16 matrix cores (either staging)
     int lds_layout;       // GEMM A slab in LDS: LAYOUT_SWIZZLE, LAYOUT_PAD or LAYOUT_PLAIN (GEMV: -1)
     int rolled;           // GEMM: 1 if the K steps of a slab run as a loop instead of fully unrolled
 };
@@ -97,6 +98,8 @@ enum LdsLayout { LAYOUT_SWIZZLE = 0, LAYOUT_PAD = 1, LAYOUT_PLAIN = 2 };
 // Variant tables, one per family (defined in the kernel sources).
 extern const Variant kGemmF32Variants[];
 extern const int kNumGemmF32Variants;
+extern const Variant kGemmF32sVariants[];   // fp32 products on the bf16 matrix cores
+extern const int kNumGemmF32sVariants;
 extern const Variant kGemmF16Variants[];
 extern const int kNumGemmF16Variants;
 extern const Variant kGemvVariants[];

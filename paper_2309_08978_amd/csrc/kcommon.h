@@ -71,4 +71,67 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+struct Split8 {
+    bf16x8 h, m, l;
+};
+
+// An fp32 product on the bf16 matrix cores: each operand is split, exactly,
+// into three bf16 parts x = h + m + l (8 + 8 + 8 significand bits, each
+// rounded to nearest even), and the product is taken as the six part products
+// down to 2^-18 of the leading one,
+//     hl + lh + mm + hm + mh + hh,
+// summed in fp32 (v_mfma_f32_32x32x16_bf16).  The three dropped products are
+// below 2^-26 of |a b|, under the rounding of one fp32 addition, and unbiased.
+//
+// Two kinds of operands do not survive the split, and the kernels take the sums
+// they reach anew on the fp32 matrix cores, straight from memory:
+//   - one that is not finite or rounds to a bf16 infinity (its parts do not add
+//     up to it), or a sum that overflows: the sum is then left not finite for
+//     good, so it is enough to test the accumulators once, at the end;
+//   - one below 2^-110 but not zero: its low parts are bf16 subnormals, which
+//     the matrix cores read as zero, an error of up to 2^-126 per product with
+//     1.  The splits keep the smallest operand they see (tiny_of), and a
+//     workgroup that saw such a one takes its sums anew if any of them is below
+//     2^-60 (the attention weights of a peaked softmax, whose sums are not,
+//     stay on the fast path).
+//
+// The smallest magnitude seen, as (bits << 1) - 1: zeros wrap to the largest.
+constexpr unsigned kTinyStart = 0xffffffffu;
+constexpr unsigned kTinyLimit = (17u << 24) - 1u;   // 2^-110
+constexpr float kTinySum = 0x1p-60f;
+
+// Eight fp32 values as three bf16 parts each (exact: x = h + m + l while h is
+// finite and l not subnormal); `tiny` takes their smallest magnitude in.  14
+// instructions per pair: three v_cvt_pk_bf16_f32, per remainder two unpacks
+// and two subtractions, and three for the minimum.
+__device__ __forceinline__ Split8 split8(f32x8 x, unsigned &tiny)
+{
+    u32x4 h, m, l;
+    auto parts = [](float a, float b, float &ra, float &rb) -> unsigned {
+        const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+        ra = a - __builtin_bit_cast(float, u << 16);
+        rb = b - __builtin_bit_cast(float, u & 0xffff0000u);
+        return u;
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float r0, r1, s0, s1, z0, z1;
+        h[q] = parts(x[2 * q], x[2 * q + 1], r0, r1);
+        m[q] = parts(r0, r1, s0, s1);
+        l[q] = parts(s0, s1, z0, z1);
+        tiny = min(min((__builtin_bit_cast(unsigned, x[2 * q]) << 1) - 1u,
+                       (__builtin_bit_cast(unsigned, x[2 * q + 1]) << 1) - 1u), tiny);
+    }
+    return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+__device__ __forceinline__ f32x16 mma_bf16(bf16x8 a, bf16x8 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
 }  // namespace nnjit

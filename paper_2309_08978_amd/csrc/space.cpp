@@ -10,25 +10,46 @@
 
 namespace nnjit {
 
-static const Variant *variant_at(int gi) {
-    if (gi < kNumGemmF32Variants) return &kGemmF32Variants[gi];
-    gi -= kNumGemmF32Variants;
-    if (gi < kNumGemmF16Variants) return &kGemmF16Variants[gi];
-    gi -= kNumGemmF16Variants;
-    if (gi < kNumGemvVariants) return &kGemvVariants[gi];
-    gi -= kNumGemvVariants;
-    return &kGemvQ4Variants[gi];
+// The variant tables, in configuration order.
+struct VariantTable {
+    const Variant *v;
+    int n;
+};
+static const VariantTable *variant_tables(int *count) {
+    static const VariantTable t[] = {{kGemmF32Variants, kNumGemmF32Variants},
+                                     {kGemmF32sVariants, kNumGemmF32sVariants},
+                                     {kGemmF16Variants, kNumGemmF16Variants},
+                                     {kGemvVariants, kNumGemvVariants},
+                                     {kGemvQ4Variants, kNumGemvQ4Variants}};
+    *count = (int)(sizeof(t) / sizeof(t[0]));
+    return t;
 }
 
-int total_variants() { return kNumGemmF32Variants + kNumGemmF16Variants + kNumGemvVariants + kNumGemvQ4Variants; }
+static const Variant *variant_at(int gi) {
+    int n = 0;
+    const VariantTable *t = variant_tables(&n);
+    for (int i = 0; i < n; ++i) {
+        if (gi < t[i].n) return &t[i].v[gi];
+        gi -= t[i].n;
+    }
+    return nullptr;
+}
+
+int total_variants() {
+    int n = 0, total = 0;
+    const VariantTable *t = variant_tables(&n);
+    for (int i = 0; i < n; ++i) total += t[i].n;
+    return total;
+}
 
 int variant_index(const Variant *v) {
-    if (v >= kGemmF32Variants && v < kGemmF32Variants + kNumGemmF32Variants) return (int)(v - kGemmF32Variants);
-    if (v >= kGemmF16Variants && v < kGemmF16Variants + kNumGemmF16Variants)
-        return kNumGemmF32Variants + (int)(v - kGemmF16Variants);
-    if (v >= kGemvVariants && v < kGemvVariants + kNumGemvVariants)
-        return kNumGemmF32Variants + kNumGemmF16Variants + (int)(v - kGemvVariants);
-    return kNumGemmF32Variants + kNumGemmF16Variants + kNumGemvVariants + (int)(v - kGemvQ4Variants);
+    int n = 0, base = 0;
+    const VariantTable *t = variant_tables(&n);
+    for (int i = 0; i < n; ++i) {
+        if (v >= t[i].v && v < t[i].v + t[i].n) return base + (int)(v - t[i].v);
+        base += t[i].n;
+    }
+    return -1;
 }
 
 const std::vector<int> &gemm_splits() {
@@ -125,7 +146,7 @@ static int64_t pow2ceil(int64_t x) {
     return p;
 }
 
-bool has_stream_k(const Variant &v) { return v.family == FAM_GEMM_F32 && v.direct_copy && v.kslices == 1; }
+bool has_stream_k(const Variant &v) { return v.family == FAM_GEMM_F32 && v.direct_copy == 1 && v.kslices == 1; }
 
 Geometry geometry_of(const Config &c, int64_t batch, int64_t M, int64_t N, int64_t K, int64_t sk_wgs) {
     Geometry g;
@@ -353,18 +374,20 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
     // heuristic 7: keep register-bound candidates (Block_core == RegLimit),
     // relaxed when too few survive.  A direct-copy variant keeps its staging
     // (the slabs in flight, a register term of Table 1 for the others) in
-    // LDS, so for it the bound that plays this role is L1Limit.
+    // LDS, so for it the bound that plays this role is L1Limit; a split-product
+    // variant keeps three planes there besides its staging registers, and
+    // either bound does.
     std::vector<Cand> kept;
     for (const Cand &c : cands) {
-        const bool direct = configs()[c.id].v->direct_copy != 0;
-        if (c.r.wg_per_cu == (direct ? c.r.lds_limit : c.r.reg_limit)) kept.push_back(c);
+        const int direct = configs()[c.id].v->direct_copy;
+        if (direct == 2 || c.r.wg_per_cu == (direct ? c.r.lds_limit : c.r.reg_limit)) kept.push_back(c);
     }
     if ((int)kept.size() < kMinSurvivors) kept = cands;
 
     // evaluation order: most workgroups per CU first, then fuller last wave,
     // larger tile, smaller split, lower id -- within each staging kind
-    // (registers / LDS direct copies), the two orders merged in turn so that
-    // the cap below never drops one kind wholesale
+    // (registers / LDS direct copies / split products), the orders merged in
+    // turn so that the cap below never drops one kind wholesale
     auto before = [](const Cand &a, const Cand &b) {
         if (a.r.wg_per_cu != b.r.wg_per_cu) return a.r.wg_per_cu > b.r.wg_per_cu;
         if (std::fabs(a.eff - b.eff) > 1e-9) return a.eff > b.eff;
@@ -372,11 +395,11 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
         if (a.split != b.split) return a.split < b.split;
         return a.id < b.id;
     };
-    std::vector<Cand> by_kind[2];
-    for (const Cand &c : kept) by_kind[configs()[c.id].v->direct_copy != 0 ? 1 : 0].push_back(c);
+    std::vector<Cand> by_kind[3];
+    for (const Cand &c : kept) by_kind[configs()[c.id].v->direct_copy].push_back(c);
     for (auto &v : by_kind) std::stable_sort(v.begin(), v.end(), before);
     std::vector<Cand> order;
-    for (size_t i = 0; i < std::max(by_kind[0].size(), by_kind[1].size()); ++i)
+    for (size_t i = 0; i < std::max({by_kind[0].size(), by_kind[1].size(), by_kind[2].size()}); ++i)
         for (auto &v : by_kind)
             if (i < v.size()) order.push_back(v[i]);
     // the lite space is the head of that order: at most kMaxTimed candidates
