@@ -36,8 +36,8 @@
  *     NNJIT_EHIP otherwise), never an abort.
  *   - Operands whose base pointers are not 16-byte aligned, or whose leading
  *     dimensions, batch strides, K or N are not multiples of 16 bytes' worth
- *     of elements, run on an element-load fallback configuration (correct,
- *     slower); this is not an error.
+ *     of elements, run on a configuration that loads from any element address
+ *     (correct; a tuned configuration may be faster); this is not an error.
  *   - Thread safety: all entry points may be called from several host
  *     threads.  Split-K scratch is kept per (device, stream), so concurrent
  *     calls on different streams do not share it; calls on one stream are
@@ -106,9 +106,10 @@ enum nnjit_kind { NNJIT_KIND_GEMM = 0, NNJIT_KIND_BATCHED = 1, NNJIT_KIND_GEMV =
 
 /* C = A . B for one product (MatMul; GEMV when M == 1).  Uses the tuned
  * configuration of this (kind, M, N, K, dtype) on the current device if
- * nnjit_tune() ran for it, else the first configuration of the shape's lite
- * space in evaluation order (the paper's predefined kernel that serves until
- * just-in-time tuning finds a better one, Sec. 3).  Never tunes implicitly.
+ * nnjit_tune() ran for it, else a predefined one chosen by the shape's sizes,
+ * or the first configuration of its lite space in evaluation order (the
+ * paper's predefined kernel that serves until just-in-time tuning finds a
+ * better one, Sec. 3).  Never tunes implicitly.
  * Returns NNJIT_OK or a negative error code. */
 int nnjit_matmul(int64_t M, int64_t N, int64_t K,
                  const void *A, int64_t lda,

@@ -41,7 +41,7 @@ template <> struct Mfma16<16> {
 __device__ __forceinline__ unsigned pack_lo(unsigned a, unsigned b) { return (a & 0xffffu) | (b << 16); }
 __device__ __forceinline__ unsigned pack_hi(unsigned a, unsigned b) { return (a >> 16) | (b & 0xffff0000u); }
 
-template <int MT, int NT, int WM, int WN, int MF, int ST, int PF, bool VEC>
+template <int MT, int NT, int WM, int WN, int MF, int ST, int PF>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_f16_kernel(GemmParams p)
 {
@@ -97,18 +97,7 @@ gemm_f16_kernel(GemmParams p)
     // see the fp32 kernel).
     const unsigned short *zero = (const unsigned short *)p.zero;
     auto ld8 = [&](const unsigned short *row, int c, int lim, bool okr) -> u32x4 {
-        u32x4 v;
-        if constexpr (VEC) {
-            v = *(const u32x4 *)((okr && c < lim) ? row + c : zero);
-        } else {
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const unsigned lo = *((okr && c + 2 * w < lim) ? row + c + 2 * w : zero);
-                const unsigned hi = *((okr && c + 2 * w + 1 < lim) ? row + c + 2 * w + 1 : zero);
-                v[w] = lo | (hi << 16);
-            }
-        }
-        return v;
+        return *(const u32x4 *)((okr && c < lim) ? row + c : zero);
     };
 
     auto gload = [&](int set, int k0) {
@@ -257,10 +246,10 @@ gemm_f16_kernel(GemmParams p)
             }
 }
 
-template <int MT, int NT, int WM, int WN, int MF, int ST, int PF, bool VEC>
+template <int MT, int NT, int WM, int WN, int MF, int ST, int PF>
 static hipError_t launch_gemm_f16(const void *params, dim3 grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((gemm_f16_kernel<MT, NT, WM, WN, MF, ST, PF, VEC>), grid, dim3(WM * WN * 64), 0, stream,
+    hipLaunchKernelGGL((gemm_f16_kernel<MT, NT, WM, WN, MF, ST, PF>), grid, dim3(WM * WN * 64), 0, stream,
                        *(const GemmParams *)params);
     return hipGetLastError();
 }
@@ -607,45 +596,43 @@ constexpr int est_regs_f16(int mt, int nt, int wm, int wn, int mf, int pf) {
 }
 constexpr int lds_f16(int mt, int nt, int st) { return st * (mt + nt) * 128; }
 
-#define NNJIT_F16_VARIANT(MT, NT, WM, WN, MF, ST, PF, VEC)                                                  \
-    {"gemm_f16_" #MT "x" #NT "x64_w" #WM "x" #WN "_m" #MF "_s" #ST "_p" #PF "_v" #VEC, FAM_GEMM_F16, MF,        \
-     (MF == 32 ? 16 : 32), MT, NT, 64, WM, WN, ST, PF, 1, (VEC ? 16 : 2), 0, 0, WM * WN * 64,                 \
+#define NNJIT_F16_VARIANT(MT, NT, WM, WN, MF, ST, PF)                                                  \
+    {"gemm_f16_" #MT "x" #NT "x64_w" #WM "x" #WN "_m" #MF "_s" #ST "_p" #PF "_vtrue", FAM_GEMM_F16, MF,        \
+     (MF == 32 ? 16 : 32), MT, NT, 64, WM, WN, ST, PF, 1, 16, 0, 0, WM * WN * 64,                 \
      lds_f16(MT, NT, ST), est_regs_f16(MT, NT, WM, WN, MF, PF),                                                \
-     (const void *)&gemm_f16_kernel<MT, NT, WM, WN, MF, ST, PF, VEC>, &launch_gemm_f16<MT, NT, WM, WN, MF, ST, PF, VEC>, \
+     (const void *)&gemm_f16_kernel<MT, NT, WM, WN, MF, ST, PF>, &launch_gemm_f16<MT, NT, WM, WN, MF, ST, PF>, \
      0, LAYOUT_SWIZZLE, 0}
 
 // The compiled fp16 configurations (K slab fixed at 64: 128-byte rows).
 #define NNJIT_F16_LIST(X) \
-    X(256, 256, 2, 2, 32, 2, 1, true) \
-    X(256, 128, 2, 2, 32, 2, 1, true) \
-    X(128, 256, 2, 2, 32, 2, 1, true) \
-    X(256, 128, 4, 2, 32, 2, 1, true) \
-    X(256, 128, 4, 2, 32, 2, 2, true) \
-    X(128, 256, 2, 4, 32, 2, 1, true) \
-    X(128, 128, 2, 2, 32, 2, 1, true) \
-    X(128, 128, 2, 2, 32, 2, 2, true) \
-    X(128, 128, 1, 2, 32, 2, 1, true) \
-    X(128, 128, 2, 1, 32, 2, 1, true) \
-    X(128, 128, 2, 2, 16, 2, 1, true) \
-    X(128, 128, 2, 2, 32, 1, 1, true) \
-    X(128, 128, 2, 2, 32, 1, 2, true) \
-    X(128, 64, 2, 1, 32, 2, 1, true) \
-    X(128, 64, 2, 2, 32, 2, 1, true) \
-    X(128, 64, 2, 2, 32, 2, 2, true) \
-    X(64, 128, 1, 2, 32, 2, 1, true) \
-    X(64, 128, 2, 2, 32, 2, 1, true) \
-    X(64, 128, 2, 2, 32, 2, 2, true) \
-    X(64, 64, 1, 1, 32, 2, 1, true) \
-    X(64, 64, 2, 2, 32, 2, 1, true) \
-    X(64, 64, 2, 2, 32, 2, 2, true) \
-    X(64, 64, 2, 2, 16, 2, 2, true) \
-    X(32, 64, 1, 2, 32, 2, 2, true) \
-    X(64, 32, 2, 1, 32, 2, 2, true) \
-    X(32, 32, 1, 1, 32, 2, 2, true) \
-    X(32, 32, 2, 2, 16, 2, 2, true) \
-    X(16, 64, 1, 4, 16, 2, 2, true) \
-    X(64, 64, 2, 2, 32, 2, 1, false) \
-    X(32, 32, 1, 1, 32, 2, 1, false)
+    X(256, 256, 2, 2, 32, 2, 1) \
+    X(256, 128, 2, 2, 32, 2, 1) \
+    X(128, 256, 2, 2, 32, 2, 1) \
+    X(256, 128, 4, 2, 32, 2, 1) \
+    X(256, 128, 4, 2, 32, 2, 2) \
+    X(128, 256, 2, 4, 32, 2, 1) \
+    X(128, 128, 2, 2, 32, 2, 1) \
+    X(128, 128, 2, 2, 32, 2, 2) \
+    X(128, 128, 1, 2, 32, 2, 1) \
+    X(128, 128, 2, 1, 32, 2, 1) \
+    X(128, 128, 2, 2, 16, 2, 1) \
+    X(128, 128, 2, 2, 32, 1, 1) \
+    X(128, 128, 2, 2, 32, 1, 2) \
+    X(128, 64, 2, 1, 32, 2, 1) \
+    X(128, 64, 2, 2, 32, 2, 1) \
+    X(128, 64, 2, 2, 32, 2, 2) \
+    X(64, 128, 1, 2, 32, 2, 1) \
+    X(64, 128, 2, 2, 32, 2, 1) \
+    X(64, 128, 2, 2, 32, 2, 2) \
+    X(64, 64, 1, 1, 32, 2, 1) \
+    X(64, 64, 2, 2, 32, 2, 1) \
+    X(64, 64, 2, 2, 32, 2, 2) \
+    X(64, 64, 2, 2, 16, 2, 2) \
+    X(32, 64, 1, 2, 32, 2, 2) \
+    X(64, 32, 2, 1, 32, 2, 2) \
+    X(32, 32, 1, 1, 32, 2, 2) \
+    X(32, 32, 2, 2, 16, 2, 2) \
+    X(16, 64, 1, 4, 16, 2, 2)
 
 // Direct-copy family: accumulators, one K step of fragments, the per-lane
 // copy geometry (2 registers per copy) and a fixed overhead; no staging.
@@ -693,8 +680,8 @@ constexpr int lds_f16t(int mt, int nt, int kt, int st) { return st * (mt + nt) *
     template __global__ void gemm_f16t_kernel<MT, NT, KT, WM, WN, MF, ST>(GemmParams);
 NNJIT_F16T_LIST(NNJIT_F16T_INST)
 
-#define NNJIT_F16_INST(MT, NT, WM, WN, MF, ST, PF, VEC) \
-    template __global__ void gemm_f16_kernel<MT, NT, WM, WN, MF, ST, PF, VEC>(GemmParams);
+#define NNJIT_F16_INST(MT, NT, WM, WN, MF, ST, PF) \
+    template __global__ void gemm_f16_kernel<MT, NT, WM, WN, MF, ST, PF>(GemmParams);
 NNJIT_F16_LIST(NNJIT_F16_INST)
 
 #if !defined(__HIP_DEVICE_COMPILE__)

@@ -131,8 +131,33 @@ gemm_f32_kernel(GemmParams p)
     // select on its result, would make the compiler wait for every
     // outstanding load before the next slab's loads are issued.
     const float *zero = (const float *)p.zero;
+    // VEC false (operands of any alignment): gfx950 loads 16 bytes from any
+    // element address, so slabs below safe_k take the same 128-bit loads; only
+    // the rest (past the K range, or where a B chunk that begins before column
+    // N would run past the operand's end) loads element by element.
+    const int safe_k = VEC ? 0 : unaligned_safe_k(p, kend);
+    const int kgp_u = __builtin_amdgcn_readfirstlane(kgp);
     auto gload = [&](int set, int it) {
         const int k0 = kbeg + (it * KS + kgp) * KT;   // this group's slab of iteration it
+        if (!VEC && kbeg + (it * KS + kgp_u) * KT + KT <= safe_k) {
+#pragma unroll
+            for (int l = 0; l < LA; ++l) {
+                const int f = tg + l * NTG;
+                const int row = f / (KT / 4), c4 = f % (KT / 4);
+                const int gm = m0 + row;
+                const bool okr = (A4 % NTG == 0 || f < A4) && gm < M;
+                ra[set][l] = *(const f32x4u *)(A + (okr ? (long long)gm * lda + k0 + c4 * 4 : (long long)k0));
+            }
+#pragma unroll
+            for (int l = 0; l < LB; ++l) {
+                const int f = tg + l * NTG;
+                const int row = f / (NT / 4), c4 = f % (NT / 4);
+                const int gn = n0 + c4 * 4;
+                const bool okr = (B4 % NTG == 0 || f < B4) && gn < N;
+                rb[set][l] = *(const f32x4u *)(B + (okr ? (long long)(k0 + row) * ldb + gn : (long long)k0 * ldb));
+            }
+            return;
+        }
 #pragma unroll
         for (int l = 0; l < LA; ++l) {
             const int f = tg + l * NTG;
@@ -1229,7 +1254,8 @@ NNJIT_F32W_LIST(NNJIT_F32W_INST)
     X(16, 64, 16, 1, 2, 16, 2, 2, 1, true) \
     X(16, 64, 32, 1, 4, 16, 2, 2, 1, true) \
     X(64, 64, 16, 2, 2, 32, 2, 1, 1, false) \
-    X(32, 32, 16, 1, 1, 32, 2, 1, 1, false)
+    X(32, 32, 16, 1, 1, 32, 2, 1, 1, false) \
+    X(32, 32, 16, 1, 1, 32, 2, 2, 4, false)
 
 // Shared-slab direct-copy variants: accumulators, one slab of fragments, the
 // per-lane copy geometry (2 registers per copy) and a fixed overhead.

@@ -41,12 +41,77 @@ namespace nnjit {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>
+// Operand types of the staged kernel: how eight elements are loaded, and the
+// planes of eight halves they become.
+template <typename T> struct Staged;
+template <> struct Staged<float> {
+    static constexpr int PL = 3;            // bf16 planes
+    struct raw { f32x4 v[2]; };
+    template <bool VEC> __device__ static __forceinline__ raw load(const float *src)
+    {
+        if constexpr (VEC) return raw{{*(const f32x4 *)src, *(const f32x4 *)(src + 4)}};
+        else return raw{{*(const f32x4u *)src, *(const f32x4u *)(src + 4)}};
+    }
+    // the first `have` elements, the others zero (`zero`: 16 zero bytes; only
+    // units that are partly in range load element by element)
+    template <bool VEC> __device__ static __forceinline__ raw load_part(const float *src, int have, const float *zero)
+    {
+        if constexpr (VEC) return raw{{*(const f32x4 *)(have > 0 ? src : zero), *(const f32x4 *)(have > 4 ? src + 4 : zero)}};
+        raw r = raw{{*(const f32x4u *)(have >= 8 ? src : zero), *(const f32x4u *)(have >= 8 ? src + 4 : zero)}};
+        if (have > 0 && have < 8) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r.v[e / 4][e % 4] = *(e < have ? src + e : zero);
+        }
+        return r;
+    }
+    __device__ static __forceinline__ void planes(const raw &r, u32x4 (&out)[3], unsigned &tiny)
+    {
+        const Split8 v = split8(__builtin_shufflevector(r.v[0], r.v[1], 0, 1, 2, 3, 4, 5, 6, 7), tiny);
+        out[0] = __builtin_bit_cast(u32x4, v.h);
+        out[1] = __builtin_bit_cast(u32x4, v.m);
+        out[2] = __builtin_bit_cast(u32x4, v.l);
+    }
+    __device__ static __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
+    {
+        return mma_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c);
+    }
+};
+template <> struct Staged<unsigned short> {   // fp16 bits
+    static constexpr int PL = 1;
+    struct raw { u32x4 v; };
+    template <bool VEC> __device__ static __forceinline__ raw load(const unsigned short *src)
+    {
+        if constexpr (VEC) return raw{*(const u32x4 *)src};
+        else return raw{load8_any(src)};
+    }
+    template <bool VEC>
+    __device__ static __forceinline__ raw load_part(const unsigned short *src, int have, const unsigned short *zero)
+    {
+        if constexpr (VEC) return raw{*(const u32x4 *)(have > 0 ? src : zero)};
+        raw r = raw{load8_any(have >= 8 ? src : zero)};
+        if (have > 0 && have < 8) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const unsigned lo = *(2 * w < have ? src + 2 * w : zero), hi = *(2 * w + 1 < have ? src + 2 * w + 1 : zero);
+                r.v[w] = lo | (hi << 16);
+            }
+        }
+        return r;
+    }
+    __device__ static __forceinline__ void planes(const raw &r, u32x4 (&out)[1], unsigned &) { out[0] = r.v; }
+    __device__ static __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
+    {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    }
+};
+
+template <typename T, int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>
 __global__ void __launch_bounds__(WM * WN * 64)
-gemm_f32s_kernel(GemmParams p)
+gemm_staged_kernel(GemmParams p)
 {
+    typedef Staged<T> O;
+    constexpr int PL = O::PL;
     typedef f32x16 acc_t;
     constexpr int ST = 3;
     constexpr int NTHR = WM * WN * 64;
@@ -56,10 +121,10 @@ gemm_f32s_kernel(GemmParams p)
     constexpr int AU = MT * ACH, BU = KT * NT / 8;   // units of one slab
     constexpr int NU = AU + BU;
     constexpr int LU = (NU + NTHR - 1) / NTHR;       // units per thread
-    constexpr int APL = AU * 16, BPL = BU * 16;      // bytes of one bf16 plane
-    constexpr int STAGE = 3 * (APL + BPL);
+    constexpr int APL = AU * 16, BPL = BU * 16;      // bytes of one plane
+    constexpr int STAGE = PL * (APL + BPL);
     constexpr int NSTEP = KT / 16;                   // matrix-core K steps per slab
-    static_assert(KT == 16 || KT == 32, "K slab");
+    static_assert(KT == 16 || KT == 32 || KT == 64, "K slab");
     static_assert(AU % 64 == 0 && BU % 64 == 0, "a wave's units are of one operand");
     static_assert(NT >= 64 && (NT & (NT - 1)) == 0, "B rows of a power of two >= 64");
     static_assert(PF == 1 || PF == ST, "staging sets");
@@ -73,9 +138,9 @@ gemm_f32s_kernel(GemmParams p)
     const int logical = xcd_remap(blockIdx.x + gx * blockIdx.z, gx * gridDim.z);
     const int M = p.M, N = p.N;
     const long long lda = p.lda, ldb = p.ldb;
-    const float *zero = (const float *)p.zero;
+    const T *zero = (const T *)p.zero;
 
-    auto a_swz = [](int row) { return KT == 16 ? ((row >> 3) & 1) : ((row >> 2) & 3); };
+    auto a_swz = [](int row) { return KT == 16 ? ((row >> 3) & 1) : KT == 32 ? ((row >> 2) & 3) : ((row >> 1) & 7); };
     auto b_swz = [](int k) { return NT >= 128 ? (((k & 3) << 1) | ((k >> 3) & 1)) : (((k >> 1) & 1) << 1); };
 
     const int z = logical / gx;
@@ -88,8 +153,8 @@ gemm_f32s_kernel(GemmParams p)
     tile_of(tile, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
     const int m0 = tm * MT, n0 = tn * NT;
     const int nk = kend > kbeg ? (kend - kbeg + KT - 1) / KT : 0;
-    const float *A = (const float *)p.A + (long long)z * p.sA;
-    const float *B = (const float *)p.B + (long long)z * p.sB;
+    const T *A = (const T *)p.A + (long long)z * p.sA;
+    const T *B = (const T *)p.B + (long long)z * p.sB;
     float *C = p.C + (long long)z * p.sC;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -104,7 +169,7 @@ gemm_f32s_kernel(GemmParams p)
     // columns of a B row (which of the two is the same for a whole wave).
     // Rows past M and units past N point at row / column 0: what they bring
     // reaches only outputs that are never stored.
-    const float *u_src[LU];
+    const T *u_src[LU];
     int u_dst[LU];
 #pragma unroll
     for (int u = 0; u < LU; ++u) {
@@ -117,14 +182,11 @@ gemm_f32s_kernel(GemmParams p)
             const int g = f - AU;
             const int k = g / (NT / 8), c = g % (NT / 8);
             u_src[u] = B + (long long)(kbeg + k) * ldb + (n0 + 8 * c < N ? n0 + 8 * c : 0);
-            u_dst[u] = 3 * APL + k * (NT * 2) + 32 * ((c >> 1) ^ b_swz(k)) + 16 * (c & 1);
+            u_dst[u] = PL * APL + k * (NT * 2) + 32 * ((c >> 1) ^ b_swz(k)) + 16 * (c & 1);
         }
     }
-    // Whole slabs whose units can be read without checks: a B unit that
-    // begins before column N and ends after it runs on into the next row,
-    // which lies inside the operand except behind its last rows.
-    int safe_k = kend;
-    if ((N & 7) != 0) safe_k = min(kend, p.K - (ldb >= 7 ? 1 : 7));
+    // whole slabs whose units can be read without checks
+    const int safe_k = unaligned_safe_k(p, kend);
     const int nfull = safe_k > kbeg ? (safe_k - kbeg) / KT : 0;
 
     // The 128-row wave tile has no register to spare for the addresses of each
@@ -132,25 +194,19 @@ gemm_f32s_kernel(GemmParams p)
     // formed where they are used.
     auto stage_base = [&](int stage) -> lds_char * {
         unsigned off = stage * STAGE;
-        if constexpr (FM >= 4) asm volatile("" : "+s"(off));
+        if constexpr (FM >= 4 && PL == 3) asm volatile("" : "+s"(off));
         return (lds_char *)smem + off;
     };
 
-    f32x4 st[PF][LU][2];
+    typename O::raw st[PF][LU];
     unsigned tiny = kTinyStart;   // the smallest operand this thread split
     auto load_full = [&](int set, int kk) {
 #pragma unroll
         for (int u = 0; u < LU; ++u) {
             if (!unit_live(u)) continue;
             const bool is_a = unit_of_a(u);
-            const float *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
-            if constexpr (VEC) {
-                st[set][u][0] = *(const f32x4 *)src;
-                st[set][u][1] = *(const f32x4 *)(src + 4);
-            } else {
-                st[set][u][0] = *(const f32x4u *)src;
-                st[set][u][1] = *(const f32x4u *)(src + 4);
-            }
+            const T *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
+            st[set][u] = O::template load<VEC>(src);
         }
     };
     // a slab that reaches past the K range or the last column: elements out
@@ -165,7 +221,7 @@ gemm_f32s_kernel(GemmParams p)
             if (!unit_live(u)) continue;
             const int f = t + u * NTHR;
             const bool is_a = unit_of_a(u);
-            const float *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
+            const T *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
             int have;   // elements of the unit in range
             if (is_a) {
                 have = kend - (kbeg + kk * KT + 8 * (f % ACH));
@@ -175,15 +231,7 @@ gemm_f32s_kernel(GemmParams p)
                 have = kbeg + kk * KT + g / (NT / 8) < kend ? (n < N ? N - n : 8) : 0;
                 if (n >= N && N < 8) have = min(have, N);
             }
-#pragma unroll
-            for (int e = 0; e < 8; e += 4) {
-                if constexpr (VEC) {
-                    st[set][u][e / 4] = *(const f32x4 *)(e < have ? src + e : zero);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) st[set][u][e / 4][q] = *(e + q < have ? src + e + q : zero);
-                }
-            }
+            st[set][u] = O::template load_part<VEC>(src, have, zero);
         }
     };
     auto load_slab = [&](int set, int kk) {
@@ -196,11 +244,10 @@ gemm_f32s_kernel(GemmParams p)
         for (int u = 0; u < LU; ++u) {
             if (!unit_live(u)) continue;
             const int pl = unit_of_a(u) ? APL : BPL;
-            const Split8 v = split8(__builtin_shufflevector(st[set][u][0], st[set][u][1], 0, 1, 2, 3, 4, 5, 6, 7), tiny);
-            lds_char *d = base + u_dst[u];
-            *(lds_u32x4 *)d = __builtin_bit_cast(u32x4, v.h);
-            *(lds_u32x4 *)(d + pl) = __builtin_bit_cast(u32x4, v.m);
-            *(lds_u32x4 *)(d + 2 * pl) = __builtin_bit_cast(u32x4, v.l);
+            u32x4 v[PL];
+            O::planes(st[set][u], v, tiny);
+#pragma unroll
+            for (int q = 0; q < PL; ++q) *(lds_u32x4 *)(base + u_dst[u] + q * pl) = v[q];
         }
     };
 
@@ -214,29 +261,32 @@ gemm_f32s_kernel(GemmParams p)
 
     const int grp = lane >> 4, tr_r = (lane >> 2) & 3, tr_q = lane & 3;
     const int tr_n = 16 * (grp & 1) + 4 * tr_q;
-    auto read_a = [&](int stage, int step, int i) -> Split8 {
+    struct AFrag { u32x4 p[PL]; };
+    auto read_a = [&](int stage, int step, int i) -> AFrag {
         const int row = wm * WTM + 32 * i + li;
         lds_char *a = stage_base(stage) + row * (KT * 2) + 16 * ((2 * step + lg) ^ a_swz(row));
-        return Split8{__builtin_bit_cast(bf16x8, *(lds_u32x4 *)a), __builtin_bit_cast(bf16x8, *(lds_u32x4 *)(a + APL)),
-                      __builtin_bit_cast(bf16x8, *(lds_u32x4 *)(a + 2 * APL))};
+        AFrag f;
+#pragma unroll
+        for (int q = 0; q < PL; ++q) f.p[q] = *(lds_u32x4 *)(a + q * APL);
+        return f;
     };
-    auto read_b = [&](int stage, int step, int j, int pl) -> bf16x8 {
+    auto read_b = [&](int stage, int step, int j, int pl) -> u32x4 {
         const int n = wn * WTN + 32 * j + tr_n;
         s16x4 h[2];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
             const int k = 16 * step + 8 * (grp >> 1) + 4 * hh + tr_r;
-            lds_char *b = stage_base(stage) + 3 * APL + pl * BPL + k * (NT * 2) +
+            lds_char *b = stage_base(stage) + PL * APL + pl * BPL + k * (NT * 2) +
                           32 * ((n >> 4) ^ b_swz(k)) + 2 * (n & 15);
             h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)b);
         }
-        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+        return __builtin_bit_cast(u32x4, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    // fragments of B of one K step: part 0 .. 2 = h, m, l
-    bf16x8 b[3][FN];
-    auto mma_part = [&](int i, const bf16x8 &x, int part) {
+    // fragments of B of one K step (three planes: h, m, l)
+    u32x4 b[PL][FN];
+    auto mma_part = [&](int i, const u32x4 &x, int part) {
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = mma_bf16(x, b[part][j], acc[i][j]);
+        for (int j = 0; j < FN; ++j) acc[i][j] = O::mma(x, b[part][j], acc[i][j]);
     };
 
     if (nk > 0) {
@@ -257,12 +307,12 @@ gemm_f32s_kernel(GemmParams p)
             load_slab(1, 4);
         }
         lds_barrier();
-        Split8 a = read_a(0, 0, 0);
+        AFrag a = read_a(0, 0, 0);
         auto read_b_part = [&](int stage, int step, int part) {
 #pragma unroll
             for (int j = 0; j < FN; ++j) b[part][j] = read_b(stage, step, j, part);
         };
-        for (int part = 2; part >= 0; --part) read_b_part(0, 0, part);
+        for (int part = PL - 1; part >= 0; --part) read_b_part(0, 0, part);
         // the products of the slab in stage u.  The next row's A fragments are
         // read while this row's products run; the last row reads the next
         // step's (or the next slab's) first ones, and each part of B again as
@@ -274,20 +324,31 @@ gemm_f32s_kernel(GemmParams p)
                 for (int i = 0; i < FM; ++i) {
                     const bool last_row = i + 1 == FM, last = last_row && q + 1 == NSTEP;
                     const int stage = last ? (u + 1) % ST : u, step = last_row ? (q + 1) % NSTEP : q;
-                    const Split8 an = read_a(stage, step, last_row ? 0 : i + 1);
-                    mma_part(i, a.h, 2);
-                    if (last_row) read_b_part(stage, step, 2);
-                    mma_part(i, a.h, 1);
-                    mma_part(i, a.m, 1);
-                    if (last_row) read_b_part(stage, step, 1);
-                    mma_part(i, a.l, 0);
-                    mma_part(i, a.m, 0);
-                    mma_part(i, a.h, 0);
-                    if (last_row) read_b_part(stage, step, 0);
+                    const AFrag an = read_a(stage, step, last_row ? 0 : i + 1);
+                    if constexpr (PL == 3) {
+                        mma_part(i, a.p[0], 2);
+                        if (last_row) read_b_part(stage, step, 2);
+                        mma_part(i, a.p[0], 1);
+                        mma_part(i, a.p[1], 1);
+                        if (last_row) read_b_part(stage, step, 1);
+                        mma_part(i, a.p[2], 0);
+                        mma_part(i, a.p[1], 0);
+                        mma_part(i, a.p[0], 0);
+                        if (last_row) read_b_part(stage, step, 0);
+                    } else {
+                        u32x4 bn[FN];
+                        if (last_row)
+#pragma unroll
+                            for (int j = 0; j < FN; ++j) bn[j] = read_b(stage, step, j, 0);
+                        mma_part(i, a.p[0], 0);
+                        if (last_row)
+#pragma unroll
+                            for (int j = 0; j < FN; ++j) b[0][j] = bn[j];
+                    }
                     a = an;
                     // keep the 128-row wave tile within its registers: no
                     // fragment read is moved up past a row of products
-                    if constexpr (FM >= 4) __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (FM >= 4 && PL == 3) __builtin_amdgcn_sched_barrier(0);
                 }
         };
         int it0 = 0;
@@ -317,47 +378,49 @@ gemm_f32s_kernel(GemmParams p)
     const int rwave = wm * WTM, cwave = wn * WTN + li;
     auto row_of = [&](int r) { return 8 * (r >> 2) + 4 * lg + (r & 3); };
 
-    // sums that the split does not serve are taken anew in fp32 (kcommon.h):
-    // not finite ones by the wave that holds them, and all of the workgroup's
-    // if it split a tiny operand and holds a tiny sum
-    float probe = 0.f, least = kTinySum;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
-                least = fminf(least, fabsf(acc[i][j][r]));
-            }
-    bool anew = __any(!(probe == 0.f));
-    if (__syncthreads_or(tiny < kTinyLimit)) anew = anew || __any(least < kTinySum);
-    if (anew) {
+    if constexpr (PL == 3) {
+        // sums that the split does not serve are taken anew in fp32 (kcommon.h):
+        // not finite ones by the wave that holds them, and all of the workgroup's
+        // if it split a tiny operand and holds a tiny sum
+        float probe = 0.f, least = kTinySum;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll 2
-        for (int k = kbeg; k < kend; k += 2) {
-            const int gk = k + lg;
-            float a[FM], b[FN];
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const int gm = m0 + rwave + 32 * i + li;
-                a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
-            }
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int gn = n0 + cwave + 32 * j;
-                b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
-            }
+                for (int r = 0; r < 16; ++r) {
+                    probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
+                    least = fminf(least, fabsf(acc[i][j][r]));
+                }
+        bool anew = __any(!(probe == 0.f));
+        if (__syncthreads_or(tiny < kTinyLimit)) anew = anew || __any(least < kTinySum);
+        if (anew) {
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll 2
+            for (int k = kbeg; k < kend; k += 2) {
+                const int gk = k + lg;
+                float a[FM], b[FN];
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+                    const int gm = m0 + rwave + 32 * i + li;
+                    a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
+                }
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const int gn = n0 + cwave + 32 * j;
+                    b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
+                }
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
         }
     }
 
@@ -379,25 +442,33 @@ gemm_f32s_kernel(GemmParams p)
             }
 }
 
-template <int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>
-static hipError_t launch_gemm_f32s(const void *params, dim3 grid, hipStream_t stream)
+template <typename T, int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>
+static hipError_t launch_gemm_staged(const void *params, dim3 grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((gemm_f32s_kernel<MT, NT, KT, WM, WN, PF, VEC>), grid, dim3(WM * WN * 64), 0, stream,
+    hipLaunchKernelGGL((gemm_staged_kernel<T, MT, NT, KT, WM, WN, PF, VEC>), grid, dim3(WM * WN * 64), 0, stream,
                        *(const GemmParams *)params);
     return hipGetLastError();
 }
 
-// accumulators, two A and two sets of B fragments (12 registers each), the
-// staging registers and a fixed overhead
-constexpr int est_regs_f32s(int mt, int nt, int kt, int wm, int wn, int pf) {
-    return (mt / wm) * (nt / wn) / 64 + 24 * (1 + (nt / wn) / 32) + (pf + 1) * (mt + nt) * kt / (wm * wn * 64) + 32;
+// accumulators, two A and one or two sets of B fragments (4 registers per
+// plane each), the staging registers and a fixed overhead
+constexpr int est_regs_staged(int pl, int mt, int nt, int kt, int wm, int wn, int pf) {
+    return (mt / wm) * (nt / wn) / 64 + 4 * pl * (2 + 2 * (nt / wn) / 32) +
+           (pf + 1) * (mt + nt) * kt * (pl == 3 ? 2 : 1) / 2 / (wm * wn * 64) + 32;
 }
-// three stages of three planes, and the flag of the workgroup-wide test
-constexpr int lds_f32s(int mt, int nt, int kt) { return 18 * kt * (mt + nt) + 256; }
+// three stages of the planes; with three planes also the flag of the
+// workgroup-wide test
+constexpr int lds_staged(int pl, int mt, int nt, int kt) { return 6 * pl * kt * (mt + nt) + (pl == 3 ? 256 : 0); }
 #define NNJIT_F32S_VARIANT(MT, NT, KT, WM, WN, PF, VEC)                                                       \
     {"gemm_f32s_" #MT "x" #NT "x" #KT "_w" #WM "x" #WN "_p" #PF "_v" #VEC, FAM_GEMM_F32, 32, 16, MT, NT, KT, WM, WN, 3, PF, \
-     1, (VEC ? 16 : 4), 0, 0, WM * WN * 64, lds_f32s(MT, NT, KT), est_regs_f32s(MT, NT, KT, WM, WN, PF),      \
-     (const void *)&gemm_f32s_kernel<MT, NT, KT, WM, WN, PF, VEC>, &launch_gemm_f32s<MT, NT, KT, WM, WN, PF, VEC>, 2, LAYOUT_SWIZZLE, 0}
+     1, (VEC ? 16 : 4), 0, 0, WM * WN * 64, lds_staged(3, MT, NT, KT), est_regs_staged(3, MT, NT, KT, WM, WN, PF), \
+     (const void *)&gemm_staged_kernel<float, MT, NT, KT, WM, WN, PF, VEC>,                                   \
+     &launch_gemm_staged<float, MT, NT, KT, WM, WN, PF, VEC>, 2, LAYOUT_SWIZZLE, 0}
+#define NNJIT_F16S_VARIANT(MT, NT, KT, WM, WN, PF, VEC)                                                       \
+    {"gemm_f16s_" #MT "x" #NT "x" #KT "_w" #WM "x" #WN "_p" #PF "_v" #VEC, FAM_GEMM_F16, 32, 16, MT, NT, KT, WM, WN, 3, PF, \
+     1, (VEC ? 16 : 2), 0, 0, WM * WN * 64, lds_staged(1, MT, NT, KT), est_regs_staged(1, MT, NT, KT, WM, WN, PF), \
+     (const void *)&gemm_staged_kernel<unsigned short, MT, NT, KT, WM, WN, PF, VEC>,                          \
+     &launch_gemm_staged<unsigned short, MT, NT, KT, WM, WN, PF, VEC>, 2, LAYOUT_SWIZZLE, 0}
 
 #define NNJIT_F32S_LIST(X) \
     X(256, 256, 16, 2, 4, 1, true) \
@@ -408,14 +479,33 @@ constexpr int lds_f32s(int mt, int nt, int kt) { return 18 * kt * (mt + nt) + 25
     X(128, 128, 16, 2, 4, 3, false) \
     X(64, 64, 16, 2, 2, 3, false)
 
-#define NNJIT_F32S_INST(MT, NT, KT, WM, WN, PF, VEC) \
-    template __global__ void gemm_f32s_kernel<MT, NT, KT, WM, WN, PF, VEC>(GemmParams);
+#define NNJIT_F16S_LIST(X) \
+    X(256, 256, 32, 2, 4, 1, true) \
+    X(256, 256, 32, 4, 2, 1, true) \
+    X(128, 256, 32, 2, 4, 3, true) \
+    X(128, 256, 64, 2, 4, 1, true) \
+    X(256, 128, 64, 4, 2, 1, true) \
+    X(128, 128, 64, 2, 4, 1, true) \
+    X(128, 128, 64, 2, 2, 1, true) \
+    X(128, 128, 32, 2, 2, 3, true) \
+    X(64, 128, 64, 2, 2, 1, true) \
+    X(64, 64, 64, 2, 2, 1, true) \
+    X(64, 64, 64, 2, 2, 3, true) \
+    X(128, 128, 32, 2, 4, 1, false) \
+    X(64, 64, 32, 2, 2, 3, false)
+
+#define NNJIT_F32S_INST(...) template __global__ void gemm_staged_kernel<float, __VA_ARGS__>(GemmParams);
+#define NNJIT_F16S_INST(...) template __global__ void gemm_staged_kernel<unsigned short, __VA_ARGS__>(GemmParams);
 NNJIT_F32S_LIST(NNJIT_F32S_INST)
+NNJIT_F16S_LIST(NNJIT_F16S_INST)
 
 #if !defined(__HIP_DEVICE_COMPILE__)
 #define NNJIT_F32S_ENTRY(...) NNJIT_F32S_VARIANT(__VA_ARGS__),
 const Variant kGemmF32sVariants[] = {NNJIT_F32S_LIST(NNJIT_F32S_ENTRY)};
 const int kNumGemmF32sVariants = sizeof(kGemmF32sVariants) / sizeof(kGemmF32sVariants[0]);
+#define NNJIT_F16S_ENTRY(...) NNJIT_F16S_VARIANT(__VA_ARGS__),
+const Variant kGemmF16sVariants[] = {NNJIT_F16S_LIST(NNJIT_F16S_ENTRY)};
+const int kNumGemmF16sVariants = sizeof(kGemmF16sVariants) / sizeof(kGemmF16sVariants[0]);
 #endif
 
 }  // namespace nnjit

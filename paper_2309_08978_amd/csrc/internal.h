@@ -100,8 +100,14 @@ extern const Variant kGemmF32Variants[];
 extern const int kNumGemmF32Variants;
 extern const Variant kGemmF32sVariants[];   // fp32 products on the bf16 matrix cores
 extern const int kNumGemmF32sVariants;
+extern const Variant kGemmF16sVariants[];   // fp16 products, staged through registers, B read transposed from LDS
+extern const int kNumGemmF16sVariants;
 extern const Variant kGemmF16Variants[];
 extern const int kNumGemmF16Variants;
+extern const Variant kGemmF32rVariants[];   // products of single rows (Mt = 1)
+extern const int kNumGemmF32rVariants;
+extern const Variant kGemmF16rVariants[];
+extern const int kNumGemmF16rVariants;
 extern const Variant kGemvVariants[];
 extern const int kNumGemvVariants;
 extern const Variant kGemvQ4Variants[];

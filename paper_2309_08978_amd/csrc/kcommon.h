@@ -39,6 +39,25 @@ __device__ __forceinline__ void tile_of(int tile, int tiles_m, int tiles_n, int 
     tn = local / rows;
 }
 
+// 16 bytes from an address aligned to an element only (gfx950 takes 128-bit
+// global loads at any address).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned short u16x8u __attribute__((ext_vector_type(8), aligned(2)));
+__device__ __forceinline__ u32x4 load8_any(const unsigned short *src)
+{
+    return __builtin_bit_cast(u32x4, *(const u16x8u *)src);
+}
+
+// Rows of B from which a chunk of up to 8 elements that begins before column N
+// can be read whole: it may run on into the next row (which no stored output
+// uses), but behind the last rows it would leave the operand.  The bound of a
+// K range [.., kend) below which every chunk of A and B can be read unchecked.
+__device__ __forceinline__ int unaligned_safe_k(const GemmParams &p, int kend)
+{
+    if ((p.N & 7) == 0) return kend;
+    return min(kend, p.K - (p.ldb >= 7 ? 1 : 7));
+}
+
 // Wait until at most N vector memory operations of this wave are pending.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()

@@ -440,9 +440,17 @@ int launch_on_stream(Device &d, const Config &cfg, const Call &c) {
     return launch(d, cfg, c, ws, g_set);
 }
 
-// First non-vector configuration of a family with split 1 (GEMM) or the split
-// that best fills the chip (GEMV): serves operands that are not 16-byte aligned.
-const Config *fallback_config(int family, const Call &c, const Device &d) {
+Shape shape_of(int kind, const Call &c) { return Shape{kind, c.dtype, c.batch, c.M, c.N, c.K}; }
+
+// The configuration that serves operands no 16-byte-load configuration can
+// run: the predefined one for any alignment (GEMM), the split that best fills
+// the chip (GEMV), the word-load configuration that does (4-bit GEMV).
+const Config *fallback_config(int kind, const Call &c, const Device &d) {
+    const int family = family_of(kind, c.dtype);
+    if (!family_is_gemv(family) && !family_is_q4(family)) {
+        const int id = predefined_config(shape_of(kind, c), false, d.limits);
+        return id >= 0 ? &configs()[id] : nullptr;
+    }
     const Config *best = nullptr;
     for (const Config &cfg : configs()) {
         if (cfg.v->family != family || cfg.v->vec_bytes == 16) continue;
@@ -451,10 +459,6 @@ const Config *fallback_config(int family, const Call &c, const Device &d) {
             // fill at most two per CU (else the one with the most)
             const Geometry g = geometry_of(cfg, c.batch, c.M, c.N, c.K);
             if (!best || g.wgs >= 2LL * d.limits.num_cus) best = &cfg;
-            continue;
-        }
-        if (!family_is_gemv(family)) {
-            if (cfg.split == 1) return &cfg;
             continue;
         }
         const Geometry g = geometry_of(cfg, c.batch, c.M, c.N, c.K);
@@ -468,17 +472,21 @@ ShapeKey key_of(int dev, int kind, const Call &c) {
     return ShapeKey(dev, kind, c.dtype, c.batch, c.M, c.N, c.K);
 }
 
-Shape shape_of(int kind, const Call &c) { return Shape{kind, c.dtype, c.batch, c.M, c.N, c.K}; }
-
-// Default configuration of a shape: first of its lite space (memoised).
+// Default configuration of a shape: the predefined one of its sizes, else the
+// first of its lite space (memoised).
 int default_config(Device &d, int kind, const Call &c) {
     const ShapeKey k = key_of(d.ordinal, kind, c);
     auto it = g_default.find(k);
     if (it != g_default.end()) return it->second;
-    LiteResult lr = lite_space(shape_of(kind, c), d.limits, &d.regs, &d.spills);
-    if (lr.ids.empty()) return fail(NNJIT_ENOCFG, "no configuration fits this shape");
-    g_default[k] = lr.ids[0];
-    return lr.ids[0];
+    const int V = vec_elems(c.dtype);
+    int id = predefined_config(shape_of(kind, c), c.N % V == 0 && c.K % V == 0, d.limits);
+    if (id < 0) {
+        LiteResult lr = lite_space(shape_of(kind, c), d.limits, &d.regs, &d.spills);
+        if (lr.ids.empty()) return fail(NNJIT_ENOCFG, "no configuration fits this shape");
+        id = lr.ids[0];
+    }
+    g_default[k] = id;
+    return id;
 }
 
 // One call on a shape that is being tuned online (caller holds g_mu).
@@ -530,7 +538,7 @@ int online_call(Device &d, int kind, const ShapeKey &key, const Call &c) {
         g_tuned[key] = tu;
         const Config &cfg = configs()[id];
         if (cfg.v->vec_bytes == 16 && !aligned_for(kind, c)) {
-            const Config *fb = fallback_config(family_of(kind, c.dtype), c, d);
+            const Config *fb = fallback_config(kind, c, d);
             if (!fb) return fail(NNJIT_ENOCFG, "no element-load fallback configuration");
             return launch_on_stream(d, *fb, c);
         }
@@ -563,7 +571,7 @@ int online_call(Device &d, int kind, const ShapeKey &key, const Call &c) {
     }
     const Config *cfg = &configs()[o.registered];
     if (cfg->v->vec_bytes == 16 && !aligned) {
-        cfg = fallback_config(family_of(kind, c.dtype), c, d);
+        cfg = fallback_config(kind, c, d);
         if (!cfg) return fail(NNJIT_ENOCFG, "no element-load fallback configuration");
     }
     t_err.clear();
@@ -616,7 +624,7 @@ int run(const Call &c, int forced) {
         }
         cfg = &configs()[id];
         if (cfg->v->vec_bytes == 16 && !aligned_for(kind, c)) {
-            cfg = fallback_config(family_of(kind, c.dtype), c, *d);
+            cfg = fallback_config(kind, c, *d);
             if (!cfg) return fail(NNJIT_ENOCFG, "no element-load fallback configuration");
         }
     }
@@ -653,7 +661,7 @@ int run_noalloc(const Call &c) {
     }
     const Config *cfg = &configs()[id];
     if (cfg->v->vec_bytes == 16 && !aligned_for(kind, c)) {
-        cfg = fallback_config(family_of(kind, c.dtype), c, *d);
+        cfg = fallback_config(kind, c, *d);
         if (!cfg) return fail(NNJIT_ENOCFG, "no element-load fallback configuration");
     }
     const Geometry g = geom(*d, *cfg, c.batch, c.M, c.N, c.K);

@@ -7,6 +7,7 @@
 #include <climits>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 
 namespace nnjit {
 
@@ -18,7 +19,10 @@ struct VariantTable {
 static const VariantTable *variant_tables(int *count) {
     static const VariantTable t[] = {{kGemmF32Variants, kNumGemmF32Variants},
                                      {kGemmF32sVariants, kNumGemmF32sVariants},
+                                     {kGemmF32rVariants, kNumGemmF32rVariants},
                                      {kGemmF16Variants, kNumGemmF16Variants},
+                                     {kGemmF16sVariants, kNumGemmF16sVariants},
+                                     {kGemmF16rVariants, kNumGemmF16rVariants},
                                      {kGemvVariants, kNumGemvVariants},
                                      {kGemvQ4Variants, kNumGemvQ4Variants}};
     *count = (int)(sizeof(t) / sizeof(t[0]));
@@ -278,7 +282,11 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
         const Variant &v = *c.v;
         if (v.family != fam) continue;
         ++out.n_enumerated;
-        if ((v.vec_bytes == 16) != vec_ok) continue;  // vector loads only where the shape allows them
+        // single-row kernels serve exactly the products with one row per
+        // slice (M = 1), whatever their alignment; vector loads only where
+        // the shape allows them
+        if (!gemv && !q4 && (v.mt == 1) != (s.M == 1)) continue;
+        if (!(v.mt == 1 && !gemv && !q4) && (v.vec_bytes == 16) != vec_ok) continue;
         const bool consistent = follows_consistent(v);
         const int gi = variant_index(&v);
         if (spills && gi < (int)spills->size() && (*spills)[gi]) continue;
@@ -409,6 +417,70 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
         out.ids.push_back(c.id);
     }
     return out;
+}
+
+// Configuration id of a variant name, unsplit (-1: not compiled).
+static int id_of(const char *name) {
+    for (const Config &c : configs())
+        if (c.split == 1 && !std::strcmp(c.v->name, name)) return c.id;
+    return -1;
+}
+
+// All lines below from device times of one MI355X (us; the first of the lite
+// space, which served before, stands in brackets).
+int predefined_config(const Shape &s, bool aligned, const nnjit_device_limits &d) {
+    if (s.kind != NNJIT_KIND_GEMM && s.kind != NNJIT_KIND_BATCHED) return -1;
+    const bool f16 = s.dtype == NNJIT_F16;
+    const int64_t cus = d.num_cus;
+    auto tiles = [&](int64_t t) { return s.batch * ceil_div(s.M, t) * ceil_div(s.N, t); };
+    if (s.M == 1) {
+        // Single rows: the widest segment whose rows of one slice are all in
+        // flight at once (8 loads of each of 256 / L row slots), so that
+        // neighbouring lanes read long runs; a longer sum takes the narrowest
+        // segment, for workgroups, and 1024 threads once 256 would go round
+        // more than about twice.  fp16, 32 slices: 1023 columns of 128 rows L16
+        // 4.4, L32 5.0, L8 5.5; 128 columns of 1023 rows L4 5.2, with 1024
+        // threads 5.6, and of 2048 rows (64 slices) 7.3 and 7.1.  fp32: 128
+        // columns of 1023 rows 1024 threads 5.7, 256 threads above 7.
+        static const int f16_id[] = {id_of("gemm_f16r_L32_t256_u8"), id_of("gemm_f16r_L16_t256_u8"),
+                                     id_of("gemm_f16r_L8_t256_u8"), id_of("gemm_f16r_L4_t256_u8"),
+                                     id_of("gemm_f16r_L4_t1024_u8")};
+        static const int f32_id[] = {id_of("gemm_f32r_L32_t256_u8"), id_of("gemm_f32r_L16_t256_u8"),
+                                     id_of("gemm_f32r_L8_t256_u8"), id_of("gemm_f32r_L8_t1024_u8")};
+        if (f16) return s.K <= 64 ? f16_id[0] : s.K <= 128 ? f16_id[1] : s.K <= 256 ? f16_id[2] : s.K <= 1024 ? f16_id[3] : f16_id[4];
+        return s.K <= 64 ? f32_id[0] : s.K <= 128 ? f32_id[1] : s.K <= 256 ? f32_id[2] : f32_id[3];
+    }
+    if (f16) {
+        // The staged kernels take any alignment at the same speed.  128 x 128
+        // tiles from two per CU on (64 x 1000 x 1000 x 64: 65, 64 x 64 tiles
+        // 72 [170]; 32 x 333 x 333 x 128, 288 tiles: 10.9 and 10.5), else 64 x
+        // 64 (32 x 336 x 128 x 336: 7.7 [12.7]; 512 x 4096 x 4096: 37 [105];
+        // 16 x 80 x 80 x 64: 4.3 [5.9]).  A long sum over few tiles is better
+        // off with a split, which the first of the lite space has (128 x 768 x
+        // 3072: 18.7 [13.7]; 16 x 4096 x 4096: 25.6 [14.2]).
+        static const int big = id_of("gemm_f16s_128x128x32_w2x4_p1_vfalse"), mid = id_of("gemm_f16s_64x64x32_w2x2_p3_vfalse");
+        if (aligned && tiles(64) < cus && s.K > 1024) return -1;
+        return s.M > 64 && s.N > 64 && tiles(128) >= 2 * cus ? big : mid;
+    }
+    // fp32: 128 x 128 split-product tiles where each CU gets one (1024 x 4096
+    // x 1024: 52, 64 x 64 tiles 64 [101]), 64 x 64 ones likewise (512 x 4096 x
+    // 4096: 129, 128 x 128 144 [223]; 32 x 333 x 128 x 333: 15.4 [22.4]).
+    static const int big = id_of("gemm_f32s_128x128x16_w2x4_p3_vfalse"), mid = id_of("gemm_f32s_64x64x16_w2x2_p3_vfalse");
+    if (s.M > 64 && s.N > 64 && tiles(128) >= cus) return big;
+    if (tiles(64) >= cus) return mid;
+    if (aligned) {
+        // 32 x 32 tiles with a K slice per wave while they are at most two per
+        // CU (64 x 768 x 768: 7.3 [10.7]; 128 x 768 x 3072: 17.9 [19.9]; 12 x
+        // 200 x 64 x 200: 5.1 [10.1]), then 64 x 64 (12 x 200 x 200 x 64: 5.1,
+        // 32 x 32 7.1 [7.0])
+        static const int w32 = id_of("gemm_f32w_32x32x16_k4_s4"), t64 = id_of("gemm_f32t_64x64x16_w2x2_s4");
+        return tiles(32) <= 2 * cus ? w32 : t64;
+    }
+    // any alignment: a long sum shared by four waves (12 x 197 x 64 x 197: 6.7,
+    // one wave 10.1; 16 x 77 x 64 x 77: 5.7 and 6.2), a short one not (12 x 197
+    // x 197 x 64: 7.7 and 6.4; 12 x 31 x 64 x 31: 5.5 and 4.6)
+    static const int k4 = id_of("gemm_f32_32x32x16_w1x1_m32_s2_p2_k4_vfalse"), k1 = id_of("gemm_f32_32x32x16_w1x1_m32_s2_p1_k1_vfalse");
+    return s.K > 64 ? k4 : k1;
 }
 
 }  // namespace nnjit

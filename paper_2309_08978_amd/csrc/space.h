@@ -101,6 +101,12 @@ struct Geometry {
 // stream-K configuration on a batch > 1 or K == 0 shape runs tiled (split 1).
 Geometry geometry_of(const Config &c, int64_t batch, int64_t M, int64_t N, int64_t K, int64_t sk_wgs = 0);
 
+// The predefined configuration of a GEMM / BatchMatMul shape: what serves it
+// until it is tuned (the paper's predefined kernel, Sec. 3), and with aligned
+// false what serves operands that no 16-byte-load configuration can run.
+// -1: the first configuration of the lite space.
+int predefined_config(const Shape &s, bool aligned, const nnjit_device_limits &d);
+
 // Index of a variant inside its family table (used to look up measured data).
 int variant_index(const Variant *v);
 int total_variants();

@@ -1,0 +1,87 @@
+"""Products whose operands no 16-byte-load configuration can run, and products
+of single rows: odd sizes, odd leading dimensions, base pointers off by one
+element, the padding between rows and slices filled with NaN.  Small integers:
+bit-exact against the oracle, through the default configuration and through
+every configuration that takes any alignment."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2309_08978_amd as nj
+import workloads
+from gpu_util import dtype_code, host
+
+pytestmark = pytest.mark.gpu
+
+# batch, M, N, K: the branches of the predefined choice and the edges of the
+# kernels (tile remainders, K of less than a slab, of whole slabs and more; N
+# of less than one load and just past one; rows per slot below and past U)
+TILES = [(12, 31, 31, 64), (12, 31, 64, 31), (5, 77, 77, 64), (5, 77, 64, 77), (3, 129, 131, 97), (16, 257, 259, 33),
+         (70, 128, 129, 40), (2, 65, 3, 7), (2, 3, 5, 1), (1, 333, 517, 203), (1, 70, 1001, 1025)]
+ROWS = [(3, 1, 5, 9), (2, 1, 1, 1), (4, 1, 8, 64), (4, 1, 9, 65), (6, 1, 1023, 128), (6, 1, 64, 511), (5, 1, 130, 129),
+        (5, 1, 127, 256), (3, 1, 128, 1025), (2, 1, 33, 2049), (2, 1, 7, 0)]
+
+
+def _operand(x, pad, shift):
+    """x [batch, rows, cols] on the GPU with a leading dimension of cols + pad,
+    a NaN-filled gap of 3 elements between slices, beginning `shift` elements
+    into its buffer.  Returns (buffer, pointer, ld, stride)."""
+    import torch
+    b, r, c = x.shape
+    ld = max(1, c + pad)
+    stride = max(1, r * ld + 3)
+    t = torch.float16 if x.dtype == np.float16 else torch.float32
+    # the buffer ends with the last element of the last row
+    buf = torch.full((shift + (b - 1) * stride + max(0, r - 1) * ld + c,), float("nan"), dtype=t, device="cuda:0")
+    if x.size:
+        idx = shift + (np.arange(b)[:, None, None] * stride + np.arange(r)[None, :, None] * ld + np.arange(c)[None, None, :])
+        buf[torch.from_numpy(idx.reshape(-1)).to("cuda:0")] = torch.from_numpy(x.reshape(-1)).to("cuda:0")
+    return buf, buf.data_ptr() + shift * buf.element_size(), ld, stride
+
+
+def _check(batch, M, N, K, dt, pads, shifts, configs):
+    import torch
+    A, B = workloads.small_int_operands([batch, M, N, K], batch, M, K, N, dt)
+    A, B = A.reshape(batch, M, K), B.reshape(batch, K, N)
+    R = oracle.matmul(A, B).reshape(batch, M, N) if K else np.zeros((batch, M, N))
+    keepA, pA, lda, sA = _operand(A, pads[0], shifts[0])
+    keepB, pB, ldb, sB = _operand(B, pads[1], shifts[1])
+    ldc, sC = N + pads[2], M * (N + pads[2]) + 1
+    for cfg in configs:
+        C = torch.full((batch * sC,), 7.5, dtype=torch.float32, device="cuda:0")
+        if cfg is None:
+            rc = nj.nnjit_batched_matmul(batch, M, N, K, pA, lda, sA, pB, ldb, sB, C, ldc, sC, dtype_code(dt))
+        else:
+            rc = nj.nnjit_matmul_config(cfg["id"], batch, M, N, K, pA, lda, sA, pB, ldb, sB, C, ldc, sC, dtype_code(dt))
+        what = "default" if cfg is None else (cfg["name"], cfg["split"])
+        assert rc == 0, (what, nj.nnjit_last_error())
+        got = host(C).reshape(batch, sC)
+        rows = got[:, :M * ldc].reshape(batch, M, ldc)
+        assert np.array_equal(rows[:, :, :N], R), what
+        assert np.all(rows[:, :, N:] == 7.5) and np.all(got[:, M * ldc:] == 7.5), (what, "wrote outside C")
+    del keepA, keepB
+
+
+def _any_alignment(dt, rows):
+    return [c for c in nj.configs() if c["family"] == "gemm_" + dt and c["vec"] < 16 and c["split"] in (1, 4)
+            and (c["Mt"] == 1) == rows]
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+@pytest.mark.parametrize("shape", TILES + ROWS)
+def test_any_alignment(dt, shape):
+    batch, M, N, K = shape
+    cfgs = [None] + [c for c in _any_alignment(dt, M == 1) if c["split"] == 1 or K >= 8 * c["Kt"]]
+    for pads, shifts in (((0, 0, 0), (0, 0)), ((1, 3, 1), (1, 0)), ((0, 6, 2), (0, 3))):
+        _check(batch, M, N, K, dt, pads, shifts, cfgs)
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(64, 256, 256, 64), (12, 200, 200, 64), (12, 200, 64, 200), (1, 64, 768, 768),
+                                   (1, 520, 512, 1032), (1, 1024, 4096, 64), (300, 128, 128, 16), (4, 1, 512, 128)])
+def test_predefined_aligned(dt, shape):
+    """The predefined configurations of aligned shapes, and of the same shapes
+    with misaligned operands."""
+    batch, M, N, K = shape
+    _check(batch, M, N, K, dt, (0, 0, 0), (0, 0), [None])
+    _check(batch, M, N, K, dt, (0, 0, 0), (1, 1), [None])
