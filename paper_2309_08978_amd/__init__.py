@@ -71,6 +71,8 @@ _lib = None
 def load(build_if_missing: bool = False) -> ctypes.CDLL:
     """Load libnnjit.so (built in-tree by ``paper_2309_08978_amd.build``)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is not None:
             return _lib
@@ -370,19 +372,60 @@ def _check_operands(A, B, C, batched: bool):
     return lds
 
 
+def _plain_lds(A, B, C, sa, sb, sc):
+    """Leading dimensions and batch strides (lda, ldb, ldc, sA, sB, sC) of
+    operands that plainly pass every check of _check_operands, read with as few
+    tensor attribute accesses as that takes; None for any other operands
+    (wrong, or right in an unusual way), which the full checks then settle."""
+    ta, tb, tc = A.stride(), B.stride(), C.stride()
+    dt = A.dtype
+    M, K, N = sa[-2], sa[-1], sb[-1]
+    lda, ldb, ldc = ta[-2], tb[-2], tc[-2]
+    if not (dt in _CODES and B.dtype is dt and C.dtype is _F32 and sb[-2] == K and sc[-2] == M and sc[-1] == N
+            and ta[-1] == 1 and tb[-1] == 1 and tc[-1] == 1
+            and lda >= K > 0 and ldb >= N > 0 and ldc >= N and M > 0
+            and A.is_cuda and B.is_cuda and C.is_cuda
+            and A.get_device() == B.get_device() == C.get_device()):
+        return None
+    if len(sa) == 2:
+        return lda, ldb, ldc, 0, 0, 0
+    if not (sa[0] == sb[0] == sc[0] and ta[0] >= 0 and tb[0] >= 0 and tc[0] >= (M - 1) * ldc + N):
+        return None
+    return lda, ldb, ldc, ta[0], tb[0], tc[0]
+
+
+_CODES: dict = {}     # torch dtype -> code; filled on first use (torch is imported lazily)
+_F32 = None
+_torch_module = None
+
+
+def _torch():
+    global _F32, _torch_module
+    if _torch_module is None:
+        import torch
+        _CODES.update({torch.float32: NNJIT_F32, torch.float16: NNJIT_F16})
+        _F32 = torch.float32
+        _torch_module = torch
+    return _torch_module
+
+
 def matmul(A, B, C=None, stream=None, cfg: Optional[int] = None):
     """C = A . B for 2-D fp32/fp16 CUDA tensors (C fp32, allocated if None)."""
-    import torch
-    if A.dim() != 2 or B.dim() != 2:
-        raise ValueError(f"matmul takes 2-D operands, got {tuple(A.shape)} . {tuple(B.shape)}")
-    M, K = A.shape
-    N = B.shape[1]
+    torch = _torch()
+    sa, sb = A.shape, B.shape
+    if len(sa) != 2 or len(sb) != 2:
+        raise ValueError(f"matmul takes 2-D operands, got {tuple(sa)} . {tuple(sb)}")
+    M, K = sa
+    N = sb[1]
     if C is None:
         C = torch.empty((M, N), dtype=torch.float32, device=A.device)
-    lda, ldb, ldc = _check_operands(A, B, C, batched=False)
-    dt = dtype_code(A)
+    sc = C.shape
+    p = _plain_lds(A, B, C, sa, sb, sc) if len(sc) == 2 else None
+    lda, ldb, ldc = p[:3] if p else _check_operands(A, B, C, batched=False)
+    dt = dtype_code(A) if not p else _CODES[A.dtype]
     if cfg is None:
-        check(nnjit_matmul(M, N, K, A, lda, B, ldb, C, ldc, dt, stream))
+        check((_lib or load()).nnjit_matmul(M, N, K, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, dt,
+                                            _stream(stream)))
     else:
         check(nnjit_matmul_config(cfg, 1, M, N, K, A, lda, 0, B, ldb, 0, C, ldc, 0, dt, stream))
     return C
@@ -390,18 +433,26 @@ def matmul(A, B, C=None, stream=None, cfg: Optional[int] = None):
 
 def batched_matmul(A, B, C=None, stream=None, cfg: Optional[int] = None):
     """C[b] = A[b] . B[b] for 3-D fp32/fp16 CUDA tensors (C fp32)."""
-    import torch
-    if A.dim() != 3 or B.dim() != 3:
-        raise ValueError(f"batched_matmul takes 3-D operands, got {tuple(A.shape)} . {tuple(B.shape)}")
-    batch, M, K = A.shape
-    N = B.shape[2]
+    torch = _torch()
+    sa, sb = A.shape, B.shape
+    if len(sa) != 3 or len(sb) != 3:
+        raise ValueError(f"batched_matmul takes 3-D operands, got {tuple(sa)} . {tuple(sb)}")
+    batch, M, K = sa
+    N = sb[2]
     if C is None:
         C = torch.empty((batch, M, N), dtype=torch.float32, device=A.device)
-    lda, ldb, ldc = _check_operands(A, B, C, batched=True)
-    dt = dtype_code(A)
-    sA, sB, sC = (int(t.stride(0)) for t in (A, B, C))
+    sc = C.shape
+    p = _plain_lds(A, B, C, sa, sb, sc) if len(sc) == 3 else None
+    if p:
+        lda, ldb, ldc, sA, sB, sC = p
+        dt = _CODES[A.dtype]
+    else:
+        lda, ldb, ldc = _check_operands(A, B, C, batched=True)
+        dt = dtype_code(A)
+        sA, sB, sC = (int(t.stride(0)) for t in (A, B, C))
     if cfg is None:
-        check(nnjit_batched_matmul(batch, M, N, K, A, lda, sA, B, ldb, sB, C, ldc, sC, dt, stream))
+        check((_lib or load()).nnjit_batched_matmul(batch, M, N, K, A.data_ptr(), lda, sA, B.data_ptr(), ldb, sB,
+                                                    C.data_ptr(), ldc, sC, dt, _stream(stream)))
     else:
         check(nnjit_matmul_config(cfg, batch, M, N, K, A, lda, sA, B, ldb, sB, C, ldc, sC, dt, stream))
     return C
@@ -411,7 +462,21 @@ def gemv_q4(x, Wq, scales, group: int, N: int, y=None, stream=None, cfg: Optiona
     """y = x . W for a 4-bit weight-only W (include/nnjit.h, nnjit_gemv_q4):
     x fp16 [K], Wq int32 [N, ldq] (uint32 code words, reinterpreted), scales
     fp16 [N, lds]; y fp32 [N] (allocated if None)."""
-    import torch
+    torch = _torch()
+    if y is not None and cfg is None:
+        # operands that plainly pass every check below, with few accesses
+        sx, sw, ss, tw, ts = x.shape, Wq.shape, scales.shape, Wq.stride(), scales.stride()
+        K = sx[0] if len(sx) == 1 else 0
+        if (K > 0 and group >= 1 and N > 1 and len(sw) == 2 and len(ss) == 2 and x.stride(0) == 1
+                and sw[0] >= N and ss[0] >= N and sw[1] >= -(-K // 8) and ss[1] >= -(-K // group)
+                and tw[1] == 1 and ts[1] == 1 and tw[0] >= sw[1] and ts[0] >= ss[1]
+                and x.dtype is torch.float16 and scales.dtype is torch.float16 and Wq.element_size() == 4
+                and y.dtype is _F32 and y.shape == (N,) and y.stride(0) == 1
+                and x.is_cuda and Wq.is_cuda and scales.is_cuda and y.is_cuda
+                and x.get_device() == Wq.get_device() == scales.get_device() == y.get_device()):
+            check((_lib or load()).nnjit_gemv_q4(N, K, group, x.data_ptr(), Wq.data_ptr(), tw[0], scales.data_ptr(),
+                                                 ts[0], y.data_ptr(), _stream(stream)))
+            return y
     if x.dim() != 1 or (x.shape[0] > 1 and x.stride(0) != 1):
         raise ValueError(f"x must be a contiguous vector, got shape {tuple(x.shape)}")
     K = int(x.shape[0])

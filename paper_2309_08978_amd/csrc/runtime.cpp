@@ -156,6 +156,14 @@ int current_device(int *dev) {
 // Initialise the calling thread's current device (under g_mu).
 int device_ready(Device **out) {
     int ord = -1;
+    // a device that is initialised already needs one query only
+    if (!g_devices.empty() && hipGetDevice(&ord) == hipSuccess) {
+        auto it = g_devices.find(ord);
+        if (it != g_devices.end() && it->second.ready && g_set_loaded) {
+            *out = &it->second;
+            return NNJIT_OK;
+        }
+    }
     int rc = current_device(&ord);
     if (rc != NNJIT_OK) return rc;
     if (!g_set_loaded) {

@@ -85,3 +85,42 @@ def test_predefined_aligned(dt, shape):
     batch, M, N, K = shape
     _check(batch, M, N, K, dt, (0, 0, 0), (0, 0), [None])
     _check(batch, M, N, K, dt, (0, 0, 0), (1, 1), [None])
+
+
+def test_binding_views_and_refusals_on_the_gpu():
+    """The tensor conveniences on operands that take the short checks and on
+    ones that need the full ones: views with padded rows, one-row and expanded
+    batches, empty products; and what is refused stays refused."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    big = torch.randint(-8, 9, (4, 40, 64), generator=g, device="cuda").float()
+    W = torch.randint(-8, 9, (4, 64, 48), generator=g, device="cuda").float()
+
+    def same(C, R):
+        return bool((C.double() == R).all())
+
+    for A, B in ((big[0], W[0]), (big[0, :, :30], W[0, :30, :17]), (big[0, 3:4], W[0]), (big[0, ::2], W[0]),
+                 (big[0, :1, :1], W[0, :1, :1])):
+        assert same(nj.matmul(A, B), A.double() @ B.double())
+    for A, B in ((big, W), (big[:, 1:2], W), (big[:, :, 5:30], W[:, 5:30, 1:]), (big[:1].expand(4, 40, 64), W),
+                 (big[1:2], W[1:2]), (big[::2], W[::2])):
+        R = torch.bmm(A.double().contiguous(), B.double().contiguous())
+        assert same(nj.batched_matmul(A, B), R)
+        C = torch.full((R.shape[0], R.shape[1] + 1, R.shape[2] + 3), 9.0, device="cuda")
+        nj.batched_matmul(A, B, C[:, :R.shape[1], :R.shape[2]])
+        assert same(C[:, :R.shape[1], :R.shape[2]], R) and bool((C[:, R.shape[1]:] == 9).all())
+    assert nj.matmul(big[0, :0], W[0]).shape == (0, 48)
+    assert bool((nj.matmul(big[0, :, :0], W[0, :0]) == 0).all())
+    bad = [(ValueError, lambda: nj.matmul(big[0], W[0].t())), (ValueError, lambda: nj.matmul(big[0].t(), big[0])),
+           (TypeError, lambda: nj.matmul(big[0], W[0].half())), (ValueError, lambda: nj.matmul(big[0], W[0].cpu())),
+           (ValueError, lambda: nj.matmul(big[0], W[0, :63])),
+           (ValueError, lambda: nj.matmul(big[0, :1].expand(40, 64), W[0])),
+           (TypeError, lambda: nj.matmul(big[0], W[0], torch.empty(40, 48, device="cuda", dtype=torch.float16))),
+           (ValueError, lambda: nj.matmul(big[0], W[0], torch.empty(1, 40, 48, device="cuda"))),
+           (ValueError, lambda: nj.batched_matmul(big, W, torch.empty(1, 40, 48, device="cuda").expand(4, 40, 48))),
+           (ValueError, lambda: nj.batched_matmul(big, W[:3])),
+           (TypeError, lambda: nj.matmul(big[0].double(), W[0].double()))]
+    for exc, call in bad:
+        with pytest.raises(exc):
+            call()
