@@ -279,6 +279,17 @@ static hipError_t launch_gemm_f16(const void *params, dim3 grid, hipStream_t str
 //
 // Pipeline: ST LDS stages; slab kk is copied into stage kk % ST while slab
 // kk - ST + 1 is multiplied; one barrier per slab.
+//
+// Where the tiles fit the chip once, what bounds the kernel is how full the
+// 256 CUs are and how many copies are in flight on each.  512 x 11008 x 4096
+// is 172 tiles of 128 x 256 (69 us), 344 of 128 x 128 (76) and 232 of 128 x
+// 192: 54.6 (846 TFLOP/s); hence the 192-wide tile, whose B rows of 12 units
+// have a swizzle of their own, sB(k) = k & 2 (row k begins on the other half
+// of the banks than row k + 1).  Four stages of 64-deep slabs and eight waves,
+// against three and four: 64 x 128 tiles, 512 x 4096 x 4096 27.2 -> 25.8 us,
+// 384 x 3072 x 1024 9.9 -> 9.0, 200 x 768 x 3072 17.9 -> 16.6; 128 x 128 (three
+// to four stages), 1000 x 4096 x 1024 15.1 -> 14.5.  Five or six stages are
+// slower again (16.2 and 10.3 on the last two), as are 192-high tiles.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
@@ -316,7 +327,12 @@ gemm_f16t_kernel(GemmParams p)
     constexpr int STAGE = A_BYTES + B_BYTES;
     constexpr int LA = A_BYTES / 1024 / NW, LB = B_BYTES / 1024 / NW;   // copies per wave and slab
     static_assert(LA * NW * 1024 == A_BYTES && LB * NW * 1024 == B_BYTES, "copies must split evenly over waves");
-    static_assert(NT >= 128 && (NT & (NT - 1)) == 0, "B swizzle needs a power-of-two row of >= 8 units");
+    // B swizzle: unit u of row k at u ^ b_swz(k).  Rows of a power of two of
+    // units (>= 8) take 3 bits; rows of 12 units begin on alternate halves of
+    // the banks, and one bit moves rows 2 and 3 of a group to the other pair
+    constexpr bool B_POW2 = (NT & (NT - 1)) == 0;
+    static_assert(NT >= 128 && (B_POW2 || (NT == 192 && MF == 32)), "B swizzle");
+    auto b_swz = [](int k) { return B_POW2 ? (((k & 3) << 1) | ((k >> 3) & 1)) : (k & 2); };
     static_assert(FM >= 1 && FN >= 1 && WTM % MF == 0 && WTN % MF == 0, "wave tile");
     static_assert((ST - 2) * (LA + LB) <= 63, "copies in flight exceed the vmcnt range");
 
@@ -375,8 +391,7 @@ gemm_f16t_kernel(GemmParams p)
     for (int j = 0; j < LB; ++j) {
         const int o = 1024 * (wave + j * NW) + 16 * lane;
         const int k = o / B_ROW, pos = (o % B_ROW) >> 4;
-        const int sb = ((k & 3) << 1) | ((k >> 3) & 1);
-        const int col = 16 * ((pos >> 1) ^ sb) + 8 * (pos & 1);
+        const int col = 16 * ((pos >> 1) ^ b_swz(k)) + 8 * (pos & 1);
         b_ok[j] = n0 + col < N;
         b_k[j] = kbeg + k;
         b_src[j] = B + (long long)(kbeg + k) * ldb + (b_ok[j] ? n0 + col : 0);
@@ -447,7 +462,7 @@ gemm_f16t_kernel(GemmParams p)
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
                 const int k = 8 * kc + 4 * hh + tr_r;
-                const int unit = (n >> 4) ^ ((tr_r << 1) | (kc & 1));
+                const int unit = (n >> 4) ^ b_swz(k);
                 h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(sbp + k * B_ROW + unit * 32 + (n & 15) * 2));
             }
             b[j] = __builtin_bit_cast(f16x8, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
@@ -667,6 +682,10 @@ constexpr int lds_f16t(int mt, int nt, int kt, int st) { return st * (mt + nt) *
     X(128, 256, 64, 2, 4, 32, 3) \
     X(128, 256, 32, 2, 4, 32, 4) \
     X(128, 256, 32, 2, 4, 32, 5) \
+    X(128, 192, 64, 4, 2, 32, 3) \
+    X(128, 192, 64, 4, 2, 32, 4) \
+    X(64, 128, 64, 2, 4, 32, 4) \
+    X(128, 128, 64, 4, 2, 32, 4) \
     X(128, 128, 64, 2, 2, 32, 2) \
     X(128, 128, 64, 2, 2, 32, 3) \
     X(128, 128, 64, 2, 2, 16, 2) \
