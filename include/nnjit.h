@@ -17,7 +17,10 @@
  *   - Shapes are passed as (M, N, K): A is M x K, B is K x N, C is M x N.
  *     (The paper writes shapes as [M, K, N]; the order here differs.)
  *   - dtype NNJIT_F32: A, B, C are fp32; products are accumulated in fp32 on
- *     the fp32 matrix cores (v_mfma_f32_*_f32), or in fp32 FMAs for GEMV.
+ *     the fp32 matrix cores (v_mfma_f32_*_f32), on the bf16 matrix cores with
+ *     every operand split in three bf16 parts (no less accurate against fp64;
+ *     operands and sums that the split does not serve are taken anew in
+ *     fp32), or in fp32 FMAs for GEMV.
  *     dtype NNJIT_F16: A and B are IEEE binary16, C is fp32, accumulation is
  *     fp32.
  *   - A, B, C are DEVICE pointers owned by the caller; the library never
@@ -238,7 +241,8 @@ int nnjit_num_configs(void);
  * (the tiles' K slabs cut evenly over one workgroup per resident slot,
  * shared tiles summed by a fix-up kernel in workgroup order), e.g.
  * "id=12 family=gemm_f32 name=... mfma=32x32x2 Mt=128 Nt=64 Kt=16 waves=2x2
- *  stages=2 prefetch=2 vec=16 split=4 threads=256 lds=...".  Returns the full length of the
+ *  stages=2 prefetch=2 vec=16 split=4 threads=256 lds=...".  A name that
+ * ends in _nG: a workgroup takes G such tiles side by side.  Returns the full length of the
  * description, or NNJIT_EINVAL. */
 int nnjit_config_info(int cfg, char *buf, int64_t len);
 

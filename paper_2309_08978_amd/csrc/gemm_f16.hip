@@ -283,9 +283,10 @@ static hipError_t launch_gemm_f16(const void *params, dim3 grid, hipStream_t str
 // Where the tiles fit the chip once, what bounds the kernel is how full the
 // 256 CUs are and how many copies are in flight on each.  512 x 11008 x 4096
 // is 172 tiles of 128 x 256 (69 us), 344 of 128 x 128 (76) and 232 of 128 x
-// 192: 54.6 (846 TFLOP/s); hence the 192-wide tile, whose B rows of 12 units
-// have a swizzle of their own, sB(k) = k & 2 (row k begins on the other half
-// of the banks than row k + 1).  Four stages of 64-deep slabs and eight waves,
+// 192: 54.6 (846 TFLOP/s); hence workgroups that take three 128 x 64 tiles side
+// by side (the A slab read once for all), whose B rows of 12 units have a
+// swizzle of their own, sB(k) = k & 2 (row k begins on the other half of the
+// banks than row k + 1).  Four stages of 64-deep slabs and eight waves,
 // against three and four: 64 x 128 tiles, 512 x 4096 x 4096 27.2 -> 25.8 us,
 // 384 x 3072 x 1024 9.9 -> 9.0, 200 x 768 x 3072 17.9 -> 16.6; 128 x 128 (three
 // to four stages), 1000 x 4096 x 1024 15.1 -> 14.5.  Five or six stages are
@@ -682,8 +683,6 @@ constexpr int lds_f16t(int mt, int nt, int kt, int st) { return st * (mt + nt) *
     X(128, 256, 64, 2, 4, 32, 3) \
     X(128, 256, 32, 2, 4, 32, 4) \
     X(128, 256, 32, 2, 4, 32, 5) \
-    X(128, 192, 64, 4, 2, 32, 3) \
-    X(128, 192, 64, 4, 2, 32, 4) \
     X(64, 128, 64, 2, 4, 32, 4) \
     X(128, 128, 64, 4, 2, 32, 4) \
     X(128, 128, 64, 2, 2, 32, 2) \
@@ -694,6 +693,20 @@ constexpr int lds_f16t(int mt, int nt, int kt, int st) { return st * (mt + nt) *
     X(64, 128, 64, 2, 2, 32, 2) \
     X(64, 128, 64, 2, 2, 32, 3) \
     X(64, 128, 64, 1, 2, 32, 3)
+
+// Workgroups that take G macro tiles of NT columns side by side.
+#define NNJIT_F16TG_VARIANT(MT, NT, G, KT, WM, WN, MF, ST)                                                  \
+    {"gemm_f16t_" #MT "x" #NT "x" #KT "_w" #WM "x" #WN "_m" #MF "_s" #ST "_n" #G, FAM_GEMM_F16, MF, (MF == 32 ? 16 : 32), \
+     MT, NT, KT, WM, WN, ST, ST - 1, 1, 16, 0, 0, WM * WN * 64, lds_f16t(MT, NT * G, KT, ST),                 \
+     est_regs_f16t(MT, NT * G, KT, WM, WN, MF), (const void *)&gemm_f16t_kernel<MT, NT * G, KT, WM, WN, MF, ST>, \
+     &launch_gemm_f16t<MT, NT * G, KT, WM, WN, MF, ST>, 1, LAYOUT_SWIZZLE, 0, G}
+#define NNJIT_F16TG_LIST(X) \
+    X(128, 64, 3, 64, 4, 2, 32, 3) \
+    X(128, 64, 3, 64, 4, 2, 32, 4)
+
+#define NNJIT_F16TG_INST(MT, NT, G, KT, WM, WN, MF, ST) \
+    template __global__ void gemm_f16t_kernel<MT, NT * G, KT, WM, WN, MF, ST>(GemmParams);
+NNJIT_F16TG_LIST(NNJIT_F16TG_INST)
 
 #define NNJIT_F16T_INST(MT, NT, KT, WM, WN, MF, ST) \
     template __global__ void gemm_f16t_kernel<MT, NT, KT, WM, WN, MF, ST>(GemmParams);
@@ -706,7 +719,9 @@ NNJIT_F16_LIST(NNJIT_F16_INST)
 #if !defined(__HIP_DEVICE_COMPILE__)
 #define NNJIT_F16_ENTRY(...) NNJIT_F16_VARIANT(__VA_ARGS__),
 #define NNJIT_F16T_ENTRY(...) NNJIT_F16T_VARIANT(__VA_ARGS__),
-const Variant kGemmF16Variants[] = {NNJIT_F16_LIST(NNJIT_F16_ENTRY) NNJIT_F16T_LIST(NNJIT_F16T_ENTRY)};
+#define NNJIT_F16TG_ENTRY(...) NNJIT_F16TG_VARIANT(__VA_ARGS__),
+const Variant kGemmF16Variants[] = {NNJIT_F16_LIST(NNJIT_F16_ENTRY) NNJIT_F16T_LIST(NNJIT_F16T_ENTRY)
+                                    NNJIT_F16TG_LIST(NNJIT_F16TG_ENTRY)};
 const int kNumGemmF16Variants = sizeof(kGemmF16Variants) / sizeof(kGemmF16Variants[0]);
 #endif
 

@@ -89,6 +89,10 @@ struct Variant {
                           // LDS, not registers); 2: fp32 products on the bf16 matrix cores (either staging)
     int lds_layout;       // GEMM A slab in LDS: LAYOUT_SWIZZLE, LAYOUT_PAD or LAYOUT_PLAIN (GEMV: -1)
     int rolled;           // GEMM: 1 if the K steps of a slab run as a loop instead of fully unrolled
+    int wg_tiles;         // GEMM: macro tiles side by side that one workgroup takes (0: one)
+
+    // columns of C that one workgroup takes
+    int wg_cols() const { return nt * (wg_tiles > 1 ? wg_tiles : 1); }
 };
 
 // LDS layouts of a GEMM's A slab: 16-byte chunk index XOR-swizzled by row,

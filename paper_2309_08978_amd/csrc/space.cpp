@@ -180,7 +180,7 @@ Geometry geometry_of(const Config &c, int64_t batch, int64_t M, int64_t N, int64
     }
     if (!family_is_gemv(v.family)) {
         g.tiles_m = (int)ceil_div(std::max<int64_t>(M, 1), v.mt);
-        g.tiles_n = (int)ceil_div(std::max<int64_t>(N, 1), v.nt);
+        g.tiles_n = (int)ceil_div(std::max<int64_t>(N, 1), v.wg_cols());
         const int64_t per = ceil_div(std::max<int64_t>(K, 1), g.split);
         g.kchunk = (int)(ceil_div(per, v.kt) * v.kt);
         const int64_t tiles = batch * g.tiles_m * (int64_t)g.tiles_n;
@@ -227,7 +227,7 @@ static bool same_group(const Variant &u, const Variant &v, int primitive) {
     if (primitive == PRIM_DIRECT) return true;
     for (int q : {PRIM_DIRECT, PRIM_LAYOUT, PRIM_UNROLL, PRIM_STAGES, PRIM_PREFETCH, PRIM_KT, PRIM_MFMA, PRIM_VEC})
         if (q != primitive && primitive_value(u, q) != primitive_value(v, q)) return false;
-    return u.kslices == v.kslices;
+    return u.kslices == v.kslices && u.wg_cols() == v.wg_cols();
 }
 
 // A variant is excluded when a fixed (consistent) setting differs from its
@@ -303,7 +303,7 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
         cd.r = r;
         const int64_t waves = ceil_div(std::max<int64_t>(g.wgs, 1), slots);
         cd.eff = (double)g.wgs / (double)(waves * slots);
-        cd.area = (int64_t)v.mt * v.nt * ((gemv || q4) ? v.kt : 1);
+        cd.area = (int64_t)v.mt * v.wg_cols() * ((gemv || q4) ? v.kt : 1);
         cd.split = c.split;
         bool fit = true;
         if (q4) {
@@ -315,7 +315,7 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
             if (v.unroll > 1 && ceil_div(nblk, v.kslices) < v.unroll) fit = false;
         } else if (!gemv) {
             // shape fit: no macro tile wider than the (power-of-two rounded) matrix
-            if (v.mt > std::max<int64_t>(16, pow2ceil(s.M)) || v.nt > std::max<int64_t>(16, pow2ceil(s.N))) fit = false;
+            if (v.mt > std::max<int64_t>(16, pow2ceil(s.M)) || v.wg_cols() > std::max<int64_t>(16, pow2ceil(s.N))) fit = false;
             const int64_t tiles = s.batch * g.tiles_m * (int64_t)g.tiles_n;
             if (c.split == kStreamK) {
                 // stream-K: only where the tiles leave the last wave of

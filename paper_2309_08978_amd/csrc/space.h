@@ -86,7 +86,8 @@ bool has_stream_k(const Variant &v);
 
 // Launch geometry of a configuration for a shape.
 struct Geometry {
-    int tiles_m = 0, tiles_n = 0;  // GEMM tiles per batch slice (GEMV: segs in tiles_n)
+    int tiles_m = 0, tiles_n = 0;  // GEMM tiles (in N: workgroups' tiles, see Variant::wg_tiles) per batch slice
+                                   // (GEMV: segs in tiles_n)
     int split = 1;                 // split-K factor of the launch (1 for stream-K)
     int kchunk = 0;
     int64_t wgs = 0;               // workgroups over the whole launch
