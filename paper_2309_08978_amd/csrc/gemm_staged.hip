@@ -290,12 +290,13 @@ gemm_staged_kernel(GemmParams p)
     };
 
     if (nk > 0) {
-        // slabs 0 and 1 into LDS, slabs 2 .. PF + 1 on their way
+        // slabs 0 and 1 into LDS, slabs 2 .. PF + 1 on their way (a set that
+        // was not loaded is not split: `tiny` sees operands only)
         if constexpr (PF == 1) {
             load_slab(0, 0);
             store_slab(0, 0);
             load_slab(0, 1);
-            store_slab(0, 1);
+            if (nk > 1) store_slab(0, 1);
             load_slab(0, 2);
         } else {
             load_slab(0, 0);
@@ -303,7 +304,7 @@ gemm_staged_kernel(GemmParams p)
             load_slab(2, 2);
             store_slab(0, 0);
             load_slab(0, 3);
-            store_slab(1, 1);
+            if (nk > 1) store_slab(1, 1);
             load_slab(1, 4);
         }
         lds_barrier();
@@ -367,7 +368,7 @@ gemm_staged_kernel(GemmParams p)
 #pragma unroll
             for (int u = 0; u < ST; ++u) {
                 const int set = PF == 1 ? 0 : (u + 2) % ST;
-                store_slab(set, (u + 2) % ST);
+                if (it0 + u + 2 < nk) store_slab(set, (u + 2) % ST);
                 load_slab(set, it0 + u + 2 + PF);
                 if (it0 + u < nk) compute(u);
                 lds_barrier();

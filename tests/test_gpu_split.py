@@ -64,3 +64,23 @@ def test_tiny_operands_keep_fp32_precision(M, N, K, scale):
         for c in _configs():
             if c["vec"] == 16 or c["split"] == 1:
                 assert np.all(np.abs(_run(c, X, B) - R) <= bound), (c["name"], c["split"])
+
+
+@pytest.mark.parametrize("K", [4, 16, 20, 32, 36, 48])
+def test_zero_sums_leave_the_other_rows_alone(K):
+    """K of one to three slabs: staging registers that no slab was loaded into
+    are not operands, so a row of zero sums changes no bit of the other rows
+    (a wave that takes its sums anew rounds them otherwise)."""
+    M, N = 300, 264
+    rng = np.random.default_rng(13)
+    A = rng.standard_normal((M, K), dtype=np.float32)
+    B = rng.standard_normal((K, N), dtype=np.float32)
+    Z = A.copy()
+    Z[::32] = 0.0
+    keep = np.arange(M) % 32 != 0
+    for c in _configs():
+        if c["split"] == 1:
+            want = _run(c, A, B)
+            for _ in range(3):
+                C = _run(c, Z, B)
+                assert np.array_equal(C[keep], want[keep]) and not C[~keep].any(), c["name"]
