@@ -510,19 +510,19 @@ gemm_f32w_kernel(GemmParams p)
     // SP: the same fragments in three bf16 parts.  A slab's eight k of a lane
     // are what the 32x32x16 instruction takes, so the layouts above serve
     // both; a wave's operands are its own, so each is split once.
-    unsigned tiny = kTinyStart;   // the smallest operand this lane split
+    float top = 0.f;   // the largest operand this lane split
     auto read_split = [&](int st, Split8 (&a)[FM], Split8 (&b)[FN]) {
         f32x8 fa[FM];
         float fb[8][FN];
         read_frags(st, fa, fb);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) a[i] = split8(fa[i], tiny);
+        for (int i = 0; i < FM; ++i) a[i] = split8(fa[i], top);
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
             f32x8 v;
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = fb[t][j];
-            b[j] = split8(v, tiny);
+            b[j] = split8(v, top);
         }
     };
     auto mma_split = [&](const Split8 (&a)[FM], const Split8 (&b)[FN]) {
@@ -649,42 +649,104 @@ gemm_f32w_kernel(GemmParams p)
 
     if constexpr (SP) {
         // sums that the split does not serve are taken anew in fp32 over this
-        // wave's slabs (kcommon.h)
-        float probe = 0.f, least = kTinySum;
+        // wave's slabs (kcommon.h).  Only those are replaced, so that a sum's
+        // bits follow from its own row and column.  1024 x 1024 x 1024 (64 x 64
+        // tiles): 19 us; with a row of zeros in every fragment, which costs the
+        // second pass, 33; with a row of infinities in every fragment 48.
+        const int rows = M - m0, cols = N - n0;
+        float probe = 0.f;
+        bool low = false;
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int j = 0; j < FN; ++j) {
+            float least = kTinySum;
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int r = 0; r < I::NR; ++r) {
                     probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
                     least = fminf(least, fabsf(acc[i][j][r]));
                 }
-        if (__any(!(probe == 0.f)) || (__any(tiny < kTinyLimit) && __any(least < kTinySum))) {
+            low = low || (least < kTinySum && 32 * j + li < cols);
+        }
+        const bool large = __any(top > kTinyMeets);
+        const bool open = nmine > 0 && (large || __any(low));
+        if (open || __any(!(probe == 0.f))) {
+            // this wave's slabs once more, through the same copies
+            auto again = [&](auto use) {
+#pragma unroll
+                for (int u = 0; u < ST - 1; ++u) copy_slab(u, u);
+                for (int t0 = 0; t0 < nmine; t0 += ST) {
+#pragma unroll
+                    for (int u = 0; u < ST; ++u) {
+                        wait_vmcnt<(ST - 2) * NCOPY>();
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        copy_slab((u + ST - 1) % ST, t0 + u + ST - 1);
+                        f32x8 a[FM];
+                        float b[8][FN];
+                        read_frags(u, a, b);
+                        if (t0 + u < nmine) use(a, b);
+                    }
+                }
+                wait_vmcnt<0>();
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            };
+            // rows of A and columns of B (bit n: the n-th of 32) that have a tiny operand
+            unsigned tiny_row[FM], tiny_col[FN];
+            unsigned la[FM], lb[FN];
+#pragma unroll
+            for (int i = 0; i < FM; ++i) la[i] = kTinyStart;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) lb[j] = kTinyStart;
+            if (open)
+                again([&](const f32x8 (&a)[FM], const float (&b)[8][FN]) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+                        for (int i = 0; i < FM; ++i) la[i] = least_of(la[i], a[i][e]);
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) lb[j] = least_of(lb[j], b[e][j]);
+                    }
+                });
+            auto both_halves = [](unsigned long long m) { return (unsigned)(m | (m >> 32)); };
+#pragma unroll
+            for (int i = 0; i < FM; ++i) tiny_row[i] = both_halves(__ballot(la[i] < kTinyLimit));
+#pragma unroll
+            for (int j = 0; j < FN; ++j) tiny_col[j] = both_halves(__ballot(lb[j] < kTinyLimit));
+            unsigned need[FM][FN];   // bit r: sum r is taken anew
+            bool some = false;
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int r = 0; r < I::NR; ++r) acc[i][j][r] = 0.f;
-#pragma unroll 1
-            for (int t = 0; t < nmine * (KT / 2); ++t) {
-                const int gk = kbeg + (wave_u + (t / (KT / 2)) * KS) * KT + 2 * (t % (KT / 2)) + lg;
-                float a[FM], b[FN];
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
-                    const int gm = m0 + 32 * i + li;
-                    a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
-                }
-#pragma unroll
                 for (int j = 0; j < FN; ++j) {
-                    const int gn = n0 + 32 * j + li;
-                    b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
+                    need[i][j] = 0;
+#pragma unroll
+                    for (int r = 0; r < I::NR; ++r) {
+                        const int row = 8 * (r >> 2) + 4 * lg + (r & 3);
+                        const bool tiny = ((tiny_row[i] >> row) | (tiny_col[j] >> li)) & 1;
+                        const float v = fabsf(acc[i][j][r]);
+                        if (!(v < __builtin_inff()) || (tiny && (large || v < kTinySum)))
+                            if (32 * j + li < cols && 32 * i + row < rows) need[i][j] |= 1u << r;
+                    }
+                    some = some || need[i][j] != 0;
                 }
+            if (__any(some)) {
+                acc_t split[FM][FN];
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) acc[i][j] = I::mma(a[i], b[j], acc[i][j]);
+                    for (int j = 0; j < FN; ++j) {
+                        split[i][j] = acc[i][j];
+#pragma unroll
+                        for (int r = 0; r < I::NR; ++r) acc[i][j][r] = 0.f;
+                    }
+                again([&](const f32x8 (&a)[FM], const float (&b)[8][FN]) { mma_slab(a, b); });
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int r = 0; r < I::NR; ++r)
+                            acc[i][j][r] = (need[i][j] >> r) & 1 ? acc[i][j][r] : split[i][j][r];
             }
         }
     }

@@ -65,12 +65,18 @@ template <> struct Staged<float> {
         }
         return r;
     }
-    __device__ static __forceinline__ void planes(const raw &r, u32x4 (&out)[3], unsigned &tiny)
+    __device__ static __forceinline__ void planes(const raw &r, u32x4 (&out)[3], float &top)
     {
-        const Split8 v = split8(__builtin_shufflevector(r.v[0], r.v[1], 0, 1, 2, 3, 4, 5, 6, 7), tiny);
+        const Split8 v = split8(__builtin_shufflevector(r.v[0], r.v[1], 0, 1, 2, 3, 4, 5, 6, 7), top);
         out[0] = __builtin_bit_cast(u32x4, v.h);
         out[1] = __builtin_bit_cast(u32x4, v.m);
         out[2] = __builtin_bit_cast(u32x4, v.l);
+    }
+    __device__ static __forceinline__ unsigned least(unsigned least, const raw &r)
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) least = least_of(least, r.v[e / 4][e % 4]);
+        return least;
     }
     __device__ static __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
     {
@@ -99,7 +105,7 @@ template <> struct Staged<unsigned short> {   // fp16 bits
         }
         return r;
     }
-    __device__ static __forceinline__ void planes(const raw &r, u32x4 (&out)[1], unsigned &) { out[0] = r.v; }
+    __device__ static __forceinline__ void planes(const raw &r, u32x4 (&out)[1], float &) { out[0] = r.v; }
     __device__ static __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
@@ -124,6 +130,12 @@ gemm_staged_kernel(GemmParams p)
     constexpr int APL = AU * 16, BPL = BU * 16;      // bytes of one plane
     constexpr int STAGE = PL * (APL + BPL);
     constexpr int NSTEP = KT / 16;                   // matrix-core K steps per slab
+    // Split products: where a slab's conversions stand.  Behind its products, the
+    // slabs kept apart in the schedule, against before them: 512 x 4096 x 4096 on
+    // 128 x 128 tiles 144 and 157 us, on 256 x 128 251 and 268; not on the largest
+    // wave tile (512 x 11008 x 4096: 492 and 444), nor on 64 x 64 tiles of any
+    // alignment (333 x 1000 x 777: 20.0 and 19.5).
+    constexpr bool LATE = PL == 3 && FM * FN < 8 && (VEC || FM * FN > 1);
     static_assert(KT == 16 || KT == 32 || KT == 64, "K slab");
     static_assert(AU % 64 == 0 && BU % 64 == 0, "a wave's units are of one operand");
     static_assert(NT >= 64 && (NT & (NT - 1)) == 0, "B rows of a power of two >= 64");
@@ -199,19 +211,19 @@ gemm_staged_kernel(GemmParams p)
     };
 
     typename O::raw st[PF][LU];
-    unsigned tiny = kTinyStart;   // the smallest operand this thread split
-    auto load_full = [&](int set, int kk) {
+    float top = 0.f;   // the largest operand this thread split
+    auto load_full = [&](typename O::raw (&dst)[LU], int kk) {
 #pragma unroll
         for (int u = 0; u < LU; ++u) {
             if (!unit_live(u)) continue;
             const bool is_a = unit_of_a(u);
             const T *src = u_src[u] + (is_a ? (long long)(kk * KT) : (long long)(kk * KT) * ldb);
-            st[set][u] = O::template load<VEC>(src);
+            dst[u] = O::template load<VEC>(src);
         }
     };
     // a slab that reaches past the K range or the last column: elements out
     // of range are read from the zero buffer (only the address is selected)
-    auto load_checked = [&](int set, int kk) {
+    auto load_checked = [&](typename O::raw (&dst)[LU], int kk) {
         // indices taken afresh from an opaque copy of the thread id, so that
         // they are not held in registers across the loop over the slabs
         int t = tid;
@@ -231,13 +243,14 @@ gemm_staged_kernel(GemmParams p)
                 have = kbeg + kk * KT + g / (NT / 8) < kend ? (n < N ? N - n : 8) : 0;
                 if (n >= N && N < 8) have = min(have, N);
             }
-            st[set][u] = O::template load_part<VEC>(src, have, zero);
+            dst[u] = O::template load_part<VEC>(src, have, zero);
         }
     };
-    auto load_slab = [&](int set, int kk) {
-        if (kk < nfull) load_full(set, kk);
-        else if (kk < nk) load_checked(set, kk);
+    auto load_units = [&](typename O::raw (&dst)[LU], int kk) {
+        if (kk < nfull) load_full(dst, kk);
+        else if (kk < nk) load_checked(dst, kk);
     };
+    auto load_slab = [&](int set, int kk) { load_units(st[set], kk); };
     auto store_slab = [&](int set, int stage) {
         lds_char *base = stage_base(stage);
 #pragma unroll
@@ -245,7 +258,7 @@ gemm_staged_kernel(GemmParams p)
             if (!unit_live(u)) continue;
             const int pl = unit_of_a(u) ? APL : BPL;
             u32x4 v[PL];
-            O::planes(st[set][u], v, tiny);
+            O::planes(st[set][u], v, top);
 #pragma unroll
             for (int q = 0; q < PL; ++q) *(lds_u32x4 *)(base + u_dst[u] + q * pl) = v[q];
         }
@@ -291,7 +304,7 @@ gemm_staged_kernel(GemmParams p)
 
     if (nk > 0) {
         // slabs 0 and 1 into LDS, slabs 2 .. PF + 1 on their way (a set that
-        // was not loaded is not split: `tiny` sees operands only)
+        // was not loaded is not split: `top` sees operands only)
         if constexpr (PF == 1) {
             load_slab(0, 0);
             store_slab(0, 0);
@@ -358,9 +371,13 @@ gemm_staged_kernel(GemmParams p)
 #pragma unroll
             for (int u = 0; u < ST; ++u) {
                 const int set = PF == 1 ? 0 : (u + 2) % ST;
+                if constexpr (LATE) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    compute(u);
+                }
                 store_slab(set, (u + 2) % ST);
-                load_full(set, it0 + u + 2 + PF);
-                compute(u);
+                load_full(st[set], it0 + u + 2 + PF);
+                if constexpr (!LATE) compute(u);
                 lds_barrier();
             }
         }
@@ -379,52 +396,6 @@ gemm_staged_kernel(GemmParams p)
     const int rwave = wm * WTM, cwave = wn * WTN + li;
     auto row_of = [&](int r) { return 8 * (r >> 2) + 4 * lg + (r & 3); };
 
-    if constexpr (PL == 3) {
-        // sums that the split does not serve are taken anew in fp32 (kcommon.h):
-        // not finite ones by the wave that holds them, and all of the workgroup's
-        // if it split a tiny operand and holds a tiny sum
-        float probe = 0.f, least = kTinySum;
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
-                    least = fminf(least, fabsf(acc[i][j][r]));
-                }
-        bool anew = __any(!(probe == 0.f));
-        if (__syncthreads_or(tiny < kTinyLimit)) anew = anew || __any(least < kTinySum);
-        if (anew) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll 2
-            for (int k = kbeg; k < kend; k += 2) {
-                const int gk = k + lg;
-                float a[FM], b[FN];
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
-                    const int gm = m0 + rwave + 32 * i + li;
-                    a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
-                }
-#pragma unroll
-                for (int j = 0; j < FN; ++j) {
-                    const int gn = n0 + cwave + 32 * j;
-                    b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
-                }
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
-        }
-    }
-
     float *out = C + (long long)m0 * p.ldc + n0;
     long long ldo = p.ldc;
     const int rows = M - m0, cols = N - n0;
@@ -441,6 +412,121 @@ gemm_staged_kernel(GemmParams p)
                 const int row = rwave + 32 * i + row_of(r), col = cwave + 32 * j;
                 if (row < rows && col < cols) out[(long long)row * ldo + col] = acc[i][j][r];
             }
+
+    if constexpr (PL == 3) {
+        // sums that the split does not serve are taken anew in fp32 (kcommon.h)
+        // and stored over the others; only those, so that a sum's bits follow from
+        // its own row and column.  1024 x 4096 x 1024 (128 x 128 tiles), 512 x 32000 x
+        // 4096 (256 x 256): 53 and 625 us; with a row of zeros in every fragment,
+        // which costs the second pass, 80 and 835; with a row of infinities in
+        // every fragment 315 and 3300.
+        float probe = 0.f;
+        bool low = false;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            float least = kTinySum;
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
+                    least = fminf(least, fabsf(acc[i][j][r]));
+                }
+            low = low || (least < kTinySum && cwave + 32 * j < cols);
+        }
+        const bool open = __syncthreads_or(low || top > kTinyMeets);
+        if (open || __any(!(probe == 0.f))) {
+            // in LDS: rows of A, groups of 8 columns of B that have a tiny operand;
+            // is there a large one
+            typedef __attribute__((address_space(3))) int lds_int;
+            lds_int *tiny_row = (lds_int *)smem, *tiny_grp = tiny_row + MT, *large = tiny_grp + NT / 8;
+            if (open) {
+                for (int t = tid; t < MT + NT / 8 + 1; t += NTHR) tiny_row[t] = 0;
+                __syncthreads();
+                if (top > kTinyMeets) *large = 1;
+                // the second pass: the units of SC slabs at a time
+                unsigned least[LU];
+#pragma unroll
+                for (int u = 0; u < LU; ++u) least[u] = kTinyStart;
+                constexpr int SC = FM >= 4 ? 2 : 1;   // (as many as leave the main loop its registers)
+                for (int kk = 0; kk < nk; kk += SC) {
+                    typename O::raw x[SC][LU];
+#pragma unroll
+                    for (int q = 0; q < SC; ++q) load_units(x[q], min(kk + q, nk - 1));
+#pragma unroll
+                    for (int q = 0; q < SC; ++q)
+#pragma unroll
+                        for (int u = 0; u < LU; ++u)
+                            if (unit_live(u)) least[u] = O::least(least[u], x[q][u]);
+                }
+#pragma unroll
+                for (int u = 0; u < LU; ++u) {
+                    const int f = tid + u * NTHR;
+                    if (least[u] >= kTinyLimit) continue;
+                    if (unit_of_a(u)) tiny_row[f / ACH] = 1;
+                    else tiny_grp[(f - AU) % (NT / 8)] = 1;
+                }
+                __syncthreads();
+            }
+            // (opaque copies: else the conditions of the stores above are kept in
+            // scalar registers, more than there are)
+            int mrows = rows, mcols = cols;
+            asm volatile("" : "+s"(mrows), "+s"(mcols));
+            unsigned need[FM][FN], some = 0;   // bit r: sum r is taken anew
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const int col = cwave + 32 * j;
+                    const bool tg = open && tiny_grp[col >> 3], meets = open && *large;
+                    need[i][j] = 0;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = rwave + 32 * i + row_of(r);
+                        const float v = fabsf(acc[i][j][r]);
+                        const bool tiny = tg || (open && tiny_row[row]);
+                        if (!(v < __builtin_inff()) || (tiny && (meets || v < kTinySum)))
+                            if (row < mrows && col < mcols) need[i][j] |= 1u << r;
+                    }
+                    some |= need[i][j];
+                }
+            if (__any(some != 0)) {
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                for (int k = kbeg; k < kend; k += 2) {
+                    const int gk = k + lg;
+                    float a[FM], b[FN];
+#pragma unroll
+                    for (int i = 0; i < FM; ++i) {
+                        const int gm = m0 + rwave + 32 * i + li;
+                        a[i] = *((gm < M && gk < kend) ? A + (long long)gm * lda + gk : zero);
+                    }
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        const int gn = n0 + cwave + 32 * j;
+                        b[j] = *((gn < N && gk < kend) ? B + (long long)gk * ldb + gn : zero);
+                    }
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+                }
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if ((need[i][j] >> r) & 1)
+                                out[(long long)(rwave + 32 * i + row_of(r)) * ldo + cwave + 32 * j] = acc[i][j][r];
+            }
+        }
+    }
 }
 
 template <typename T, int MT, int NT, int KT, int WM, int WN, int PF, bool VEC>

@@ -110,24 +110,36 @@ struct Split8 {
 // they reach anew on the fp32 matrix cores, straight from memory:
 //   - one that is not finite or rounds to a bf16 infinity (its parts do not add
 //     up to it), or a sum that overflows: the sum is then left not finite for
-//     good, so it is enough to test the accumulators once, at the end;
-//   - one below 2^-110 but not zero: its low parts are bf16 subnormals, which
-//     the matrix cores read as zero, an error of up to 2^-126 per product with
-//     1.  The splits keep the smallest operand they see (tiny_of), and a
-//     workgroup that saw such a one takes its sums anew if any of them is below
-//     2^-60 (the attention weights of a peaked softmax, whose sums are not,
-//     stay on the fast path).
+//     good, so it is enough to test the sums once, at the end;
+//   - one below 2^-110 but not zero (tiny): its last bits are below the
+//     smallest bf16 subnormal, 2^-133 (conversion and matrix cores keep
+//     subnormals), and what they lose, up to 2^-134, counts times the other
+//     operand.  If all sums are at least 2^-60 and no operand is above 2^32,
+//     K products lose at most K 2^-101, which the rounding of K fp32 additions
+//     covers; so tiny operands are looked for, with a second pass over the
+//     operands, only where a sum is below 2^-60 or an operand above 2^32.  A sum
+//     of a row of A or column of B that has a tiny one is then taken anew if it
+//     is below 2^-60 or the other matrix has one above 2^32.  Sums of a peaked
+//     softmax's weights times ordinary values thus cost nothing, and zero sums
+//     of zero rows or columns the second pass.
 //
-// The smallest magnitude seen, as (bits << 1) - 1: zeros wrap to the largest.
+// The second pass takes the smallest magnitude in as (bits << 1) - 1: zeros wrap
+// to the largest.  (The bits are taken of a scalar: of an element of a vector,
+// __builtin_bit_cast takes those of the first one.)
 constexpr unsigned kTinyStart = 0xffffffffu;
 constexpr unsigned kTinyLimit = (17u << 24) - 1u;   // 2^-110
 constexpr float kTinySum = 0x1p-60f;
+constexpr float kTinyMeets = 0x1p32f;
+__device__ __forceinline__ unsigned least_of(unsigned least, float x)
+{
+    return min(least, (__builtin_bit_cast(unsigned, x) << 1) - 1u);
+}
 
 // Eight fp32 values as three bf16 parts each (exact: x = h + m + l while h is
-// finite and l not subnormal); `tiny` takes their smallest magnitude in.  14
-// instructions per pair: three v_cvt_pk_bf16_f32, per remainder two unpacks
-// and two subtractions, and three for the minimum.
-__device__ __forceinline__ Split8 split8(f32x8 x, unsigned &tiny)
+// finite and x zero or at least 2^-110); `top` takes their largest magnitude
+// in.  12 instructions per pair: three v_cvt_pk_bf16_f32, per remainder two
+// unpacks and two subtractions, and a v_max3_f32.
+__device__ __forceinline__ Split8 split8(f32x8 x, float &top)
 {
     u32x4 h, m, l;
     auto parts = [](float a, float b, float &ra, float &rb) -> unsigned {
@@ -142,8 +154,7 @@ __device__ __forceinline__ Split8 split8(f32x8 x, unsigned &tiny)
         h[q] = parts(x[2 * q], x[2 * q + 1], r0, r1);
         m[q] = parts(r0, r1, s0, s1);
         l[q] = parts(s0, s1, z0, z1);
-        tiny = min(min((__builtin_bit_cast(unsigned, x[2 * q]) << 1) - 1u,
-                       (__builtin_bit_cast(unsigned, x[2 * q + 1]) << 1) - 1u), tiny);
+        top = fmaxf(fmaxf(fabsf(x[2 * q]), fabsf(x[2 * q + 1])), top);
     }
     return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }

@@ -1,7 +1,7 @@
 """fp32 products on the bf16 matrix cores (operands split in three bf16 parts):
 what the split does not serve -- operands that are not finite, that round to a
-bf16 infinity, sums that overflow, operands whose low parts are subnormal --
-comes out as fp32 arithmetic gives it."""
+bf16 infinity, sums that overflow, operands whose last bits are below the
+smallest bf16 subnormal -- comes out as fp32 arithmetic gives it."""
 import numpy as np
 import pytest
 
@@ -64,6 +64,85 @@ def test_tiny_operands_keep_fp32_precision(M, N, K, scale):
         for c in _configs():
             if c["vec"] == 16 or c["split"] == 1:
                 assert np.all(np.abs(_run(c, X, B) - R) <= bound), (c["name"], c["split"])
+
+
+def _bound(A, B):
+    K = A.shape[1]
+    return (K + 4) * 2.0 ** -24 * (np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)) + K * 2.0 ** -148
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES + [(300, 520, 72)])
+@pytest.mark.parametrize("a,b", [(1e-37, 1e36), (1e-36, 1e30), (1e-34, 1e25), (1e-39, 1e36), (3e-41, 1.0)])
+def test_tiny_operands_that_meet_large_ones(M, N, K, a, b):
+    """Tiny operands times large ones, in either order, whole or in one row and
+    one column beside ordinary ones: the same bound as above, also where the
+    sums are not small."""
+    rng = np.random.default_rng(14)
+    A0 = rng.uniform(0.5, 1, (M, K)).astype(np.float32) * rng.choice([-1, 1], (M, K)).astype(np.float32)
+    B0 = rng.uniform(0.5, 1, (K, N)).astype(np.float32) * rng.choice([-1, 1], (K, N)).astype(np.float32)
+    few_a, few_b = A0.copy(), B0.copy()
+    few_a[17, 5:] *= np.float32(a)      # a row [1, a, ...] meets a column [1, b, ...]
+    few_b[5:, N - 2] *= np.float32(b)
+    whole_a, whole_b = A0 * np.float32(a), B0 * np.float32(b)
+    for A, B in ((whole_a, whole_b), (few_a, few_b), (few_a, whole_b)):
+        for X, Y in ((A, B), (np.ascontiguousarray(B.T), np.ascontiguousarray(A.T))):
+            R = X.astype(np.float64) @ Y.astype(np.float64)
+            bound = _bound(X, Y)
+            for c in _configs():
+                if c["vec"] < 16 or Y.shape[1] % 4 == 0:
+                    assert np.all(np.abs(_run(c, X, Y) - R) <= bound), (c["name"], c["split"])
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES + [(300, 520, 72)])
+def test_a_single_tiny_operand_at_any_place(M, N, K):
+    """Row r of A (and column r of B) is zero but for one tiny value, none of
+    them the first of the eight that are split together."""
+    rng = np.random.default_rng(17)
+    at = lambda n: 8 * (np.arange(n) % (K // 8)) + 1 + np.arange(n) % 7
+    A, B = np.zeros((M, K), np.float32), rng.uniform(0.5, 1, (K, N)).astype(np.float32)
+    A[np.arange(M), at(M)] = (rng.uniform(1, 2, M) * 2.0 ** rng.integers(-140, -110, M)).astype(np.float32)
+    At, Bt = rng.uniform(0.5, 1, (M, K)).astype(np.float32), np.zeros((K, N), np.float32)
+    Bt[at(N), np.arange(N)] = (rng.uniform(1, 2, N) * 2.0 ** rng.integers(-140, -110, N)).astype(np.float32)
+    for X, Y in ((A, B), (At, Bt)):
+        R = X.astype(np.float64) @ Y.astype(np.float64)
+        for c in _configs():
+            assert np.all(np.abs(_run(c, X, Y) - R) <= 2.0 ** -24 * np.abs(R) * 2 + 2.0 ** -149), (c["name"], c["split"])
+
+
+@pytest.mark.parametrize("lo", [2.0 ** -110, 2.0 ** -106, 2.0 ** -103])
+def test_operands_at_the_limit_of_the_split(lo):
+    """Every operand of A in [lo, 8 lo): at and above 2^-110 the three parts
+    hold all bits (the low ones as bf16 subnormals), so the sums, all far below
+    the test of small sums, are right without it."""
+    M, N, K = SHAPES[1]
+    rng = np.random.default_rng(15)
+    A = (rng.uniform(1, 8, (M, K)) * lo).astype(np.float32)
+    B = rng.uniform(0.5, 1, (K, N)).astype(np.float32)
+    R = A.astype(np.float64) @ B.astype(np.float64)
+    for c in _configs():
+        assert np.all(np.abs(_run(c, A, B) - R) <= _bound(A, B)), (c["name"], c["split"])
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES + [(300, 520, 72)])
+def test_only_the_sums_concerned_are_taken_anew(M, N, K):
+    """Rows of weights of which one is tiny, rows and columns of zeros, a row
+    that overflows: every other sum keeps its bits."""
+    rng = np.random.default_rng(16)
+    A = rng.uniform(0.5, 1, (M, K)).astype(np.float32)
+    B = rng.standard_normal((K, N), dtype=np.float32)
+    X, Y = A.copy(), B.copy()
+    X[3, 2], X[40, K - 1] = 1e-35, 1e-40
+    X[5], X[33] = 0.0, 0.0
+    X[64] = 3.3e38
+    Y[:, 7] = 0.0
+    rows = np.setdiff1d(np.arange(M), [3, 40, 5, 33, 64])
+    cols = np.setdiff1d(np.arange(N), [7])
+    for c in _configs():
+        want, C = _run(c, A, B), _run(c, X, Y)
+        assert np.array_equal(C[np.ix_(rows, cols)], want[np.ix_(rows, cols)]), (c["name"], c["split"])
+        assert not C[[5, 33]].any() and not C[rows][:, 7].any() and not C[[3, 40], 7].any(), (c["name"], c["split"])
+        R = X[[3, 40]].astype(np.float64) @ Y.astype(np.float64)
+        assert np.all(np.abs(C[[3, 40]] - R) <= _bound(X[[3, 40]], Y)), (c["name"], c["split"])
 
 
 @pytest.mark.parametrize("K", [4, 16, 20, 32, 36, 48])
