@@ -163,3 +163,18 @@ def test_zero_sums_leave_the_other_rows_alone(K):
             for _ in range(3):
                 C = _run(c, Z, B)
                 assert np.array_equal(C[keep], want[keep]) and not C[~keep].any(), c["name"]
+
+
+@pytest.mark.parametrize("K", [8, 40, 200, 1024])
+@pytest.mark.parametrize("value", [1.0038986, 1.0, 1.9999999, 0.7])
+def test_equal_operands(K, value):
+    """The dropped part products of equal operands have one sign: up to 2^-24 of
+    each product (1.0038986 comes nearest), besides one rounding per part
+    product and 16 k, and those of the sums over waves and splits."""
+    M, N = 72, 136
+    v = np.float32(value)
+    A, B = np.full((M, K), v), np.full((K, N), v)
+    R = K * float(v) * float(v)
+    for c in _configs():
+        C = _run(c, A, B)
+        assert np.all(np.abs(C - R) <= (1 + 6 * -(-K // 16) + 8) * 2.0 ** -24 * R), (c["name"], c["split"])
