@@ -476,6 +476,17 @@ const Config *fallback_config(int kind, const Call &c, const Device &d) {
     return best;
 }
 
+// Is a call served by the fallback instead of the shape's configuration: its
+// operands take no 16-byte loads, or (predefined configurations) are misaligned
+// though the shape is aligned, and the configuration, split for the shape's
+// sake, would take any alignment but scratch too, which such calls never need.
+bool needs_fallback(int kind, const Config &cfg, const Call &c, bool predefined) {
+    const int V = vec_elems(c.dtype);
+    const bool gemm = kind == NNJIT_KIND_GEMM || kind == NNJIT_KIND_BATCHED;
+    const bool spare = predefined && gemm && cfg.split > 1 && c.N % V == 0 && c.K % V == 0;
+    return (cfg.v->vec_bytes == 16 || spare) && !aligned_for(kind, c);
+}
+
 ShapeKey key_of(int dev, int kind, const Call &c) {
     return ShapeKey(dev, kind, c.dtype, c.batch, c.M, c.N, c.K);
 }
@@ -614,6 +625,7 @@ int run(const Call &c, int forced) {
     } else {
         const int kind = kind_of(c);
         int id = -1;
+        bool predefined = false;
         const int env_force = g_set.force_config;
         if (env_force >= 0 && env_force < (int)configs().size() &&
             configs()[env_force].v->family == family_of(kind, c.dtype))
@@ -628,10 +640,11 @@ int run(const Call &c, int forced) {
             } else {
                 id = default_config(*d, kind, c);
                 if (id < 0) return id;
+                predefined = true;
             }
         }
         cfg = &configs()[id];
-        if (cfg->v->vec_bytes == 16 && !aligned_for(kind, c)) {
+        if (needs_fallback(kind, *cfg, c, predefined)) {
             cfg = fallback_config(kind, c, *d);
             if (!cfg) return fail(NNJIT_ENOCFG, "no element-load fallback configuration");
         }
@@ -655,6 +668,7 @@ int run_noalloc(const Call &c) {
     if (rc != NNJIT_OK) return rc;
     const int kind = kind_of(c);
     int id = -1;
+    bool predefined = false;
     const int env_force = g_set.force_config;
     if (env_force >= 0 && env_force < (int)configs().size() && configs()[env_force].v->family == family_of(kind, c.dtype))
         id = env_force;
@@ -664,11 +678,11 @@ int run_noalloc(const Call &c) {
         auto on = g_online.find(key);
         if (it != g_tuned.end()) id = it->second.cfg;
         else if (on != g_online.end()) id = on->second.registered;
-        else id = default_config(*d, kind, c);
+        else id = default_config(*d, kind, c), predefined = true;
         if (id < 0) return id;
     }
     const Config *cfg = &configs()[id];
-    if (cfg->v->vec_bytes == 16 && !aligned_for(kind, c)) {
+    if (needs_fallback(kind, *cfg, c, predefined)) {
         cfg = fallback_config(kind, c, *d);
         if (!cfg) return fail(NNJIT_ENOCFG, "no element-load fallback configuration");
     }

@@ -419,11 +419,60 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
     return out;
 }
 
-// Configuration id of a variant name, unsplit (-1: not compiled).
-static int id_of(const char *name) {
+// Configuration id of a variant name and split (-1: not compiled).
+static int id_of(const char *name, int split = 1) {
     for (const Config &c : configs())
-        if (c.split == 1 && !std::strcmp(c.v->name, name)) return c.id;
+        if (c.split == split && !std::strcmp(c.v->name, name)) return c.id;
     return -1;
+}
+
+// The largest compiled split of `tiles` workgroups that keeps them at most
+// `most` and leaves each at least `rows` of the K rows (1: none does).
+static int split_within(int64_t tiles, int64_t most, int64_t K, int64_t rows) {
+    int best = 1;
+    for (int s : gemm_splits())
+        if (tiles * s <= most && K >= rows * s) best = s;
+    return best;
+}
+
+// Single rows (M = 1).  The widest segment whose rows of one slice are all in
+// flight at once (8 loads of each of 256 / L row slots), so that neighbouring
+// lanes read long runs; a longer sum takes the narrowest segment, for
+// workgroups, and 1024 threads once 256 would go round more than about twice.
+// fp16, 32 slices: 1023 columns of 128 rows L16 4.4, L32 5.0, L8 5.5; 128
+// columns of 1023 rows L4 5.2, with 1024 threads 5.6, and of 2048 rows (64
+// slices) 7.3 and 7.1.  fp32: 128 columns of 1023 rows 1024 threads 5.7, 256
+// threads above 7.
+// fp32 has half the columns per lane and twice the bytes: where the slices and
+// segments fill the chip anyway, long runs count for more than workgroups, so
+// the segment is the widest of which every CU gets about four (8 slices of 11008
+// columns and 1024 rows: L16 62, L8 with 1024 threads 92; 32 of 4096 and 1024:
+// L32 92, 118; 256 of 1024 and 512: L64 92, 136), up to eight of the widest
+// (512 of 1024 and 256: L8 90, L64 111); and 1024 threads only while there are
+// at most two narrow ones per CU (2 of 11008 and 1024: 21.5, 25.1).
+// Few segments and a long sum, at least two rounds of 1024 threads: the
+// narrowest with 256 threads, split to about four workgroups per CU (fp32, 8
+// slices of 128 columns: 4096 rows 9.1, unsplit 14.7; 16384 rows 25 and 77;
+// fp16 16384 rows 12 and 31), from 16 tiles of 64 columns on: those shapes
+// took scratch before there were row kernels, the smaller ones did not and can
+// be captured without a run before.
+static int predefined_row(const Shape &s, bool aligned, const nnjit_device_limits &d) {
+    static const char *const f16_name[] = {"gemm_f16r_L4_t256_u8", "gemm_f16r_L8_t256_u8", "gemm_f16r_L16_t256_u8",
+                                           "gemm_f16r_L32_t256_u8", "gemm_f16r_L4_t1024_u8"};
+    static const char *const f32_name[] = {"gemm_f32r_L8_t256_u8", "gemm_f32r_L16_t256_u8", "gemm_f32r_L32_t256_u8",
+                                           "gemm_f32r_L64_t256_u8", "gemm_f32r_L8_t1024_u8"};
+    const bool f16 = s.dtype == NNJIT_F16;
+    const int64_t cus = d.num_cus;
+    auto segments = [&](int columns) { return s.batch * ceil_div(s.N, columns); };
+    if (aligned && s.K >= (f16 ? 4096 : 2048) && segments(32) <= cus / 2 && segments(64) >= cus / 16)
+        return id_of(f16 ? f16_name[0] : f32_name[0], split_within(segments(32), 4 * cus, s.K, 1));
+    if (f16) return id_of(f16_name[s.K <= 64 ? 3 : s.K <= 128 ? 2 : s.K <= 256 ? 1 : s.K <= 1024 ? 0 : 4]);
+    const bool many = segments(256) >= 8 * cus;
+    int wide = 0;
+    while (!many && wide < 3 && 2 * segments(32 << (wide + 1)) >= 7 * cus) ++wide;
+    const int by_sum = s.K <= (many ? 64 : 32) ? 2 : s.K <= 128 ? 1 : 0;
+    if (s.K <= 256 || segments(32) > 2 * cus) return id_of(f32_name[std::max(wide, by_sum)]);
+    return id_of(f32_name[4]);
 }
 
 // All lines below from device times of one MI355X (us; the first of the lite
@@ -433,23 +482,7 @@ int predefined_config(const Shape &s, bool aligned, const nnjit_device_limits &d
     const bool f16 = s.dtype == NNJIT_F16;
     const int64_t cus = d.num_cus;
     auto tiles = [&](int64_t t) { return s.batch * ceil_div(s.M, t) * ceil_div(s.N, t); };
-    if (s.M == 1) {
-        // Single rows: the widest segment whose rows of one slice are all in
-        // flight at once (8 loads of each of 256 / L row slots), so that
-        // neighbouring lanes read long runs; a longer sum takes the narrowest
-        // segment, for workgroups, and 1024 threads once 256 would go round
-        // more than about twice.  fp16, 32 slices: 1023 columns of 128 rows L16
-        // 4.4, L32 5.0, L8 5.5; 128 columns of 1023 rows L4 5.2, with 1024
-        // threads 5.6, and of 2048 rows (64 slices) 7.3 and 7.1.  fp32: 128
-        // columns of 1023 rows 1024 threads 5.7, 256 threads above 7.
-        static const int f16_id[] = {id_of("gemm_f16r_L32_t256_u8"), id_of("gemm_f16r_L16_t256_u8"),
-                                     id_of("gemm_f16r_L8_t256_u8"), id_of("gemm_f16r_L4_t256_u8"),
-                                     id_of("gemm_f16r_L4_t1024_u8")};
-        static const int f32_id[] = {id_of("gemm_f32r_L32_t256_u8"), id_of("gemm_f32r_L16_t256_u8"),
-                                     id_of("gemm_f32r_L8_t256_u8"), id_of("gemm_f32r_L8_t1024_u8")};
-        if (f16) return s.K <= 64 ? f16_id[0] : s.K <= 128 ? f16_id[1] : s.K <= 256 ? f16_id[2] : s.K <= 1024 ? f16_id[3] : f16_id[4];
-        return s.K <= 64 ? f32_id[0] : s.K <= 128 ? f32_id[1] : s.K <= 256 ? f32_id[2] : f32_id[3];
-    }
+    if (s.M == 1) return predefined_row(s, aligned, d);
     if (f16) {
         // The staged kernels take any alignment at the same speed.  128 x 128
         // tiles from two per CU on (64 x 1000 x 1000 x 64: 65, 64 x 64 tiles

@@ -87,6 +87,58 @@ def test_predefined_aligned(dt, shape):
     _check(batch, M, N, K, dt, (0, 0, 0), (1, 1), [None])
 
 
+# the predefined choice for single rows: every segment width, the split, and its
+# neighbours at either end
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(8, 1, 128, 4096), (8, 1, 128, 4095), (8, 1, 127, 4096), (8, 1, 64, 4096), (2, 1, 1032, 2048),
+                                   (257, 1, 264, 40), (257, 1, 130, 136), (130, 1, 1032, 24), (600, 1, 72, 520),
+                                   (2, 1, 8200, 264), (3, 1, 2056, 300)])
+def test_predefined_single_rows(dt, shape):
+    batch, M, N, K = shape
+    _check(batch, M, N, K, dt, (0, 0, 0), (0, 0), [None])
+    _check(batch, M, N, K, dt, (0, 0, 0), (1, 1), [None])
+    _check(batch, M, N, K, dt, (0, 3, 1), (0, 0), [None])
+
+
+def _captured(batch, M, N, K, dt, shift):
+    """The default call under capture on a stream that has run nothing before:
+    the return code, and whether two replays give the product."""
+    import torch
+    A, B = workloads.small_int_operands([batch, M, N, K], batch, M, K, N, dt)
+    A, B = A.reshape(batch, M, K), B.reshape(batch, K, N)
+    R = oracle.matmul(A, B).reshape(batch, M, N)
+    keepA, pA, lda, sA = _operand(A, 0, shift)
+    keepB, pB, ldb, sB = _operand(B, 0, shift)
+    if not shift:   # slices without a gap, so that the operands are aligned
+        keepA, keepB = (torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0") for x in (A, B))
+        pA, lda, sA, pB, ldb, sB = keepA.data_ptr(), K, M * K, keepB.data_ptr(), N, K * N
+    C = torch.zeros((batch, M, N), dtype=torch.float32, device="cuda:0")
+    call = lambda st: nj.nnjit_batched_matmul(batch, M, N, K, pA, lda, sA, pB, ldb, sB, C.data_ptr(), N, M * N,
+                                              dtype_code(dt), st)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        rc = call(stream)
+    for _ in range(2 if rc == 0 else 0):
+        C.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        assert np.array_equal(host(C).reshape(batch, M, N), R)
+    return rc
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+def test_predefined_split_takes_scratch_only_where_it_did(dt):
+    """A split needs scratch, which a stream under capture cannot get: misaligned
+    operands and shapes that a split never served run under capture at once."""
+    assert _captured(8, 1, 128, 4096, dt, 1) == 0      # misaligned operands of a split shape
+    assert _captured(2, 1, 64, 8192, dt, 0) == 0       # too few columns for a split before
+    assert _captured(8, 1, 128, 4095, dt, 0) == 0      # a shape of any alignment
+    assert _captured(8, 1, 128, 4096, dt, 0) == nj.NNJIT_EHIP
+    assert "capture" in nj.nnjit_last_error()
+
+
 def test_binding_views_and_refusals_on_the_gpu():
     """The tensor conveniences on operands that take the short checks and on
     ones that need the full ones: views with padded rows, one-row and expanded
