@@ -498,11 +498,15 @@ int default_config(Device &d, int kind, const Call &c) {
     auto it = g_default.find(k);
     if (it != g_default.end()) return it->second;
     const int V = vec_elems(c.dtype);
-    int id = predefined_config(shape_of(kind, c), c.N % V == 0 && c.K % V == 0, d.limits);
-    if (id < 0) {
-        LiteResult lr = lite_space(shape_of(kind, c), d.limits, &d.regs, &d.spills);
-        if (lr.ids.empty()) return fail(NNJIT_ENOCFG, "no configuration fits this shape");
-        id = lr.ids[0];
+    const bool aligned = c.N % V == 0 && c.K % V == 0;
+    const Shape shape = shape_of(kind, c);
+    int id = predefined_config(shape, aligned, d.limits);
+    const int split = id < 0 ? -1 : predefined_split(shape, id, d.limits);
+    if (id < 0 || split != id) {
+        LiteResult lr = lite_space(shape, d.limits, &d.regs, &d.spills);
+        if (id < 0 && lr.ids.empty()) return fail(NNJIT_ENOCFG, "no configuration fits this shape");
+        if (id < 0) id = lr.ids[0];
+        else if (takes_scratch(shape, aligned, lr, d.limits)) id = split;
     }
     g_default[k] = id;
     return id;

@@ -499,6 +499,16 @@ int predefined_config(const Shape &s, bool aligned, const nnjit_device_limits &d
     // x 1024: 52, 64 x 64 tiles 64 [101]), 64 x 64 ones likewise (512 x 4096 x
     // 4096: 129, 128 x 128 144 [223]; 32 x 333 x 128 x 333: 15.4 [22.4]).
     static const int big = id_of("gemm_f32s_128x128x16_w2x4_p3_vfalse"), mid = id_of("gemm_f32s_64x64x16_w2x2_p3_vfalse");
+    // Up to 16 rows: 16-row tiles, which the lite space begins with, over many
+    // columns (8 x 32000 x 4096: 131, 64 x 64 tiles 158; 16 x 11008 x 4096: 41,
+    // 32 x 32 tiles 56; 32 x 16 x 1024 x 128: 7.8 and 9.2; not fewer: 16 x 8192 x
+    // 1024 15.2 and 10.5), and for long sums that 32 x 32 tiles share over less
+    // than seven eighths of the CUs (14 x 2584 x 6320, 162 workgroups: 22.8 and
+    // 25.6; 8 x 6976 x 4752, 218: 30.0 and 31.4; 16 x 4096 x 4096, 256: 25.1 and 19.7).
+    if (aligned && s.M <= 16) {
+        const int64_t t = tiles(32);
+        if (t > cus || (t > cus / 4 && s.K >= 2048 && 8 * t * split_within(t, cus, s.K, 256) < 7 * cus)) return -1;
+    }
     if (s.M > 64 && s.N > 64 && tiles(128) >= cus) return big;
     if (tiles(64) >= cus) return mid;
     if (aligned) {
@@ -514,6 +524,32 @@ int predefined_config(const Shape &s, bool aligned, const nnjit_device_limits &d
     // x 197 x 64: 7.7 and 6.4; 12 x 31 x 64 x 31: 5.5 and 4.6)
     static const int k4 = id_of("gemm_f32_32x32x16_w1x1_m32_s2_p2_k4_vfalse"), k1 = id_of("gemm_f32_32x32x16_w1x1_m32_s2_p1_k1_vfalse");
     return s.K > 64 ? k4 : k1;
+}
+
+// From sums of 1024 on, 256 and more to a workgroup, up to a workgroup per CU
+// (us; unsplit in brackets): fp32 32 x 32 tiles, 256 x 256 x 4096 in four 12.1 [22.4],
+// 8 x 16 x 128 x 4096 in eight 9.5 [21.7], 40 x 1024 x 11008 in four 21.7 [54], 33 x
+// 513 x 8193 in four 26.5 [73]; fp16 64 x 64, 33 x 513 x 8193 in sixteen 13.5 [52].
+int predefined_split(const Shape &s, int id, const nnjit_device_limits &d) {
+    const Config &c = configs()[id];
+    if (s.M == 1 || s.K < 1024) return id;
+    const int64_t tiles = s.batch * ceil_div(s.M, c.v->mt) * ceil_div(s.N, c.v->wg_cols());
+    const int split = split_within(tiles, d.num_cus, s.K, 256);
+    if (split == 1 || c.split != 1) return id;
+    for (const Config &o : configs())
+        if (o.v == c.v && o.split == split) return o.id;
+    return id;
+}
+
+bool takes_scratch(const Shape &s, bool aligned, const LiteResult &lite, const nnjit_device_limits &d) {
+    if (aligned || s.dtype != NNJIT_F16) return !lite.ids.empty() && configs()[lite.ids[0]].split > 1;
+    // (32 x 32 tiles with 64-deep slabs, the smallest split that gives every CU
+    // a workgroup)
+    const int64_t tiles = s.batch * ceil_div(s.M, 32) * ceil_div(s.N, 32);
+    if (tiles >= d.num_cus || tiles * 16 < d.num_cus) return false;
+    int64_t fill = 1;
+    while (tiles * fill < d.num_cus) fill <<= 1;
+    return s.K >= 2 * fill * 64;
 }
 
 }  // namespace nnjit

@@ -108,6 +108,15 @@ Geometry geometry_of(const Config &c, int64_t batch, int64_t M, int64_t N, int64
 // -1: the first configuration of the lite space.
 int predefined_config(const Shape &s, bool aligned, const nnjit_device_limits &d);
 
+// The same configuration with the split that fills the chip with a long sum
+// over few tiles; the configuration itself where none does.
+int predefined_split(const Shape &s, int id, const nnjit_device_limits &d);
+
+// May the predefined configuration of this shape take scratch?  Where a split
+// one served it before there were predefined ones by size; a call on any other
+// shape can be captured, and made without allocation, without a run before.
+bool takes_scratch(const Shape &s, bool aligned, const LiteResult &lite, const nnjit_device_limits &d);
+
 // Index of a variant inside its family table (used to look up measured data).
 int variant_index(const Variant *v);
 int total_variants();

@@ -100,6 +100,18 @@ def test_predefined_single_rows(dt, shape):
     _check(batch, M, N, K, dt, (0, 3, 1), (0, 0), [None])
 
 
+# long sums over few tiles (split where a split served them before, and the
+# lengths and tile counts around that), up to 16 rows over few and many columns
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(1, 39, 1264, 5072), (1, 40, 1256, 1016), (8, 16, 128, 4096), (1, 256, 256, 4096),
+                                   (1, 33, 513, 8193), (8, 23, 53, 1621), (1, 16, 4096, 1024), (1, 16, 8200, 1032),
+                                   (1, 9, 8192, 40), (1, 14, 2584, 2064), (32, 7, 1032, 72)])
+def test_predefined_long_sums_and_few_rows(dt, shape):
+    batch, M, N, K = shape
+    _check(batch, M, N, K, dt, (0, 0, 0), (0, 0), [None])
+    _check(batch, M, N, K, dt, (0, 0, 0), (1, 1), [None])
+
+
 def _captured(batch, M, N, K, dt, shift):
     """The default call under capture on a stream that has run nothing before:
     the return code, and whether two replays give the product."""
@@ -135,6 +147,8 @@ def test_predefined_split_takes_scratch_only_where_it_did(dt):
     assert _captured(8, 1, 128, 4096, dt, 1) == 0      # misaligned operands of a split shape
     assert _captured(2, 1, 64, 8192, dt, 0) == 0       # too few columns for a split before
     assert _captured(8, 1, 128, 4095, dt, 0) == 0      # a shape of any alignment
+    assert _captured(8, 16, 128, 4096, dt, 1) == 0
+    assert _captured(1, 40, 72, 8192, dt, 0) == 0      # more splits than there are would be needed
     assert _captured(8, 1, 128, 4096, dt, 0) == nj.NNJIT_EHIP
     assert "capture" in nj.nnjit_last_error()
 
