@@ -86,7 +86,8 @@ struct Variant {
     const void *kernel;   // device function (attribute queries)
     LaunchFn launch;
     int direct_copy;      // 0: slabs staged through registers; 1: global -> LDS by direct copies (staging in
-                          // LDS, not registers); 2: fp32 products on the bf16 matrix cores (either staging)
+                          // LDS, not registers); 2: fp32 products on the bf16 matrix cores (either staging),
+                          // and fp16 ones staged by the same kernel
     int lds_layout;       // GEMM A slab in LDS: LAYOUT_SWIZZLE, LAYOUT_PAD or LAYOUT_PLAIN (GEMV: -1)
     int rolled;           // GEMM: 1 if the K steps of a slab run as a loop instead of fully unrolled
     int wg_tiles;         // GEMM: macro tiles side by side that one workgroup takes (0: one)

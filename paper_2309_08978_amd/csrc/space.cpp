@@ -237,7 +237,8 @@ static bool same_group(const Variant &u, const Variant &v, int primitive) {
 bool follows_consistent(const Variant &v) {
     for (const ConsistentSetting &c : consistent_settings()) {
         if (c.family != v.family) continue;
-        if (!(v.direct_copy ? c.direct_copy : c.reg_staged)) continue;
+        // (the settings were measured for the first two kinds of staging only)
+        if (v.direct_copy == 2 || !(v.direct_copy ? c.direct_copy : c.reg_staged)) continue;
         if (primitive_value(v, c.primitive) == c.value) continue;
         for (const Config &u : configs())
             if (u.split == 1 && primitive_value(*u.v, c.primitive) == c.value && same_group(*u.v, v, c.primitive))
@@ -382,9 +383,9 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
     // heuristic 7: keep register-bound candidates (Block_core == RegLimit),
     // relaxed when too few survive.  A direct-copy variant keeps its staging
     // (the slabs in flight, a register term of Table 1 for the others) in
-    // LDS, so for it the bound that plays this role is L1Limit; a split-product
-    // variant keeps three planes there besides its staging registers, and
-    // either bound does.
+    // LDS, so for it the bound that plays this role is L1Limit; a variant of the
+    // third kind keeps planes of halves there besides its staging registers,
+    // and either bound does.
     std::vector<Cand> kept;
     for (const Cand &c : cands) {
         const int direct = configs()[c.id].v->direct_copy;
@@ -411,7 +412,10 @@ LiteResult lite_space(const Shape &s, const nnjit_device_limits &d, const std::v
         for (auto &v : by_kind)
             if (i < v.size()) order.push_back(v[i]);
     // the lite space is the head of that order: at most kMaxTimed candidates
-    // are ever evaluated on the device
+    // are ever evaluated on the device.  (Third-kind candidates take the place of
+    // up to 13 register-staged ones at the end of the order.  Over 49 shapes
+    // where that happens, the fastest of those took 1.13 to 2.8 times as long
+    // as the fastest of the lite space.)
     for (const Cand &c : order) {
         if ((int)out.ids.size() >= kMaxTimed) break;
         out.ids.push_back(c.id);

@@ -2,6 +2,7 @@
 entry point include/nnjit.h declares, validates arguments before touching
 HIP, and its lite-space builder follows the Table 1 resource model and
 heuristics of the paper (Sec. 5.2)."""
+import itertools
 import json
 import os
 import re
@@ -308,6 +309,24 @@ def test_consistent_table_is_generated_from_the_stored_measurement(lib):
     # the rule excludes something (when the table fixes anything)
     if fixed:
         assert any(mb.excluded_by(c, fixed, cfgs) for c in cfgs)
+
+
+def test_third_kind_of_staging_is_not_excluded(lib):
+    """The fixed settings compare the first two kinds of staging; the third
+    (direct=2) is subject to none of them, in either place the rule is written:
+    every aligned fp16 configuration of that kind is in some lite space."""
+    from paper_2309_08978_amd import microbench as mb
+    fixed = mb.consistent_settings(json.load(open(mb.MEASUREMENT))["runs"])
+    cfgs = nj.configs()
+    third = [c for c in cfgs if c.get("direct") == 2]
+    assert third and not any(mb.excluded_by(c, fixed, cfgs) for c in third)
+    dev = nj.mi355x_limits()
+    seen = set()
+    for M, N, K in itertools.product((48, 64, 128, 512, 2048), (64, 256, 1024, 4096), (64, 512, 4096)):
+        for batch in (1, 16):
+            kind = nj.NNJIT_KIND_GEMM if batch == 1 else nj.NNJIT_KIND_BATCHED
+            seen |= {cfgs[i]["name"] for i in nj.nnjit_lite_space(kind, nj.NNJIT_F16, batch, M, N, K, dev)[0]}
+    assert {c["name"] for c in third if c["family"] == "gemm_f16" and c["vec"] == 16} <= seen
 
 
 @pytest.mark.parametrize("N,K,G", [(4096, 4096, 128), (12288, 4096, 128), (4096, 11008, 128), (32000, 4096, 128),
