@@ -380,7 +380,8 @@ int nnjit_cache_save(const char *path);
  * for another device signature, unknown configuration names, configurations
  * that do not fit the entry's kind and dtype, and malformed lines are skipped
  * (a line whose first candidate is unknown is skipped whole; unknown later
- * candidates are dropped).  Loading merges: a shape already in the cache
+ * candidates are dropped; a configuration that a later build removed is read
+ * as the one that took its place).  Loading merges: a shape already in the cache
  * keeps whichever entry has the faster measured time, so databases from
  * identical devices can be loaded one after another.  Returns the number of
  * valid entries read (>= 0), or NNJIT_EINVAL (unreadable file) / NNJIT_EHIP. */

@@ -1378,6 +1378,16 @@ int nnjit_cache_load(const char *path) {
     char line[4096];
     int n = 0;
     auto find_id = [](const char *name, int split) {
+        // databases outlive configurations: what now serves the shapes of those
+        // that were removed, with the same split
+        static const char *const successor[][2] = {
+            {"gemm_f16_64x64x64_w2x2_m32_s2_p1_vfalse", "gemm_f16s_64x64x32_w2x2_p3_vfalse"},
+            {"gemm_f16_32x32x64_w1x1_m32_s2_p1_vfalse", "gemm_f16s_64x64x32_w2x2_p3_vfalse"},
+            {"gemm_f16s_128x128x64_w2x4_p1_vtrue", "gemm_f16s_128x128x32_w2x4_p1_vfalse"},
+            {"gemm_f16s_128x128x32_w2x2_p3_vtrue", "gemm_f16s_128x128x32_w2x4_p1_vfalse"},
+        };
+        for (const auto &s : successor)
+            if (strcmp(name, s[0]) == 0) name = s[1];
         for (const Config &c : configs())
             if (c.split == split && strcmp(c.v->name, name) == 0) return c.id;
         return -1;
@@ -1403,7 +1413,8 @@ int nnjit_cache_load(const char *path) {
         while ((int)tu.ranked.size() < kRanked && sscanf(rest, "%159s %d %lf%n", name, &split, &us, &more) == 3) {
             rest += more;
             const int rid = find_id(name, split);
-            if (rid >= 0 && configs()[rid].v->family == family_of(kind, dtype)) tu.ranked.emplace_back(rid, us);
+            const bool twice = std::any_of(tu.ranked.begin(), tu.ranked.end(), [&](const auto &r) { return r.first == rid; });
+            if (rid >= 0 && !twice && configs()[rid].v->family == family_of(kind, dtype)) tu.ranked.emplace_back(rid, us);
         }
         // merging databases: a shape already known keeps the faster measurement
         const ShapeKey key(d->ordinal, kind, dtype, batch, M, N, K);

@@ -12,7 +12,7 @@ import oracle
 from oracle import accept
 import paper_2309_08978_amd as nj
 import workloads
-from tests.gpu_util import dev, host, kind_of, dtype_code
+from tests.gpu_util import dev, gpu_matmul, host, kind_of, dtype_code
 
 pytestmark = pytest.mark.gpu
 
@@ -222,6 +222,30 @@ def test_kernel_database_roundtrip(tmp_path):
     assert nj.check(nj.nnjit_tune(op.M, op.N, op.K, nj.NNJIT_F32)) == cfg
     assert nj.nnjit_last_tune_stats_ex()["cache_hit"] == 1
     assert nj.nnjit_cache_load(str(tmp_path / "missing.txt")) == nj.NNJIT_EINVAL
+
+
+def test_database_lines_of_removed_configurations(tmp_path):
+    """A line that names configurations of an earlier build which were removed
+    is read as their successors, and serves its shape."""
+    nj.nnjit_cache_clear()
+    nj.check(nj.nnjit_tune(64, 64, 64, nj.NNJIT_F16))
+    path = tmp_path / "db.txt"
+    nj.check(nj.nnjit_cache_save(str(path)))
+    sig = next(l for l in path.read_text().splitlines() if not l.startswith("#")).split()[0]
+    path.write_text(f"{sig} 1 1 5 77 77 64 gemm_f16_64x64x64_w2x2_m32_s2_p1_vfalse 1 9.0 "
+                    "gemm_f16_32x32x64_w1x1_m32_s2_p1_vfalse 1 9.5\n"
+                    f"{sig} 0 1 1 70 1001 1025 gemm_f16_32x32x64_w1x1_m32_s2_p1_vfalse 4 9.0\n"
+                    f"{sig} 0 1 1 256 256 512 gemm_f16s_128x128x64_w2x4_p1_vtrue 2 9.0\n")
+    nj.nnjit_cache_clear()
+    assert nj.check(nj.nnjit_cache_load(str(path))) == 3
+    assert len(nj.nnjit_cached_ranked(nj.NNJIT_KIND_BATCHED, nj.NNJIT_F16, 5, 77, 77, 64)) == 1
+    for batch, M, N, K, split in ((5, 77, 77, 64, 1), (1, 70, 1001, 1025, 4), (1, 256, 256, 512, 2)):
+        kind = nj.NNJIT_KIND_GEMM if batch == 1 else nj.NNJIT_KIND_BATCHED
+        got = nj.configs()[nj.nnjit_cached_config(kind, nj.NNJIT_F16, batch, M, N, K)]
+        assert got["name"].startswith("gemm_f16s_") and got["split"] == split
+        A, B = workloads.small_int_operands([batch, M, N, K], batch, M, K, N, "f16")
+        assert np.array_equal(gpu_matmul(A, B), oracle.matmul(A, B))
+    nj.nnjit_cache_clear()
 
 
 def test_ranked_candidates_and_database_merge(tmp_path):
