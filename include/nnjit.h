@@ -241,9 +241,9 @@ int nnjit_num_configs(void);
  * (the tiles' K slabs cut evenly over one workgroup per resident slot,
  * shared tiles summed by a fix-up kernel in workgroup order), e.g.
  * "id=12 family=gemm_f32 name=... mfma=32x32x2 Mt=128 Nt=64 Kt=16 waves=2x2
- *  stages=2 prefetch=2 vec=16 split=4 threads=256 lds=...".  A name that
- * ends in _nG: a workgroup takes G such tiles side by side.  Returns the full length of the
- * description, or NNJIT_EINVAL. */
+ *  stages=2 prefetch=2 vec=16 split=4 threads=256 lds=... wg_tiles=1" (a
+ * workgroup takes wg_tiles such tiles side by side, wg_tiles * Nt columns).
+ * Returns the full length of the description, or NNJIT_EINVAL. */
 int nnjit_config_info(int cfg, char *buf, int64_t len);
 
 /* Device description used by the resource model (Table 1's hardware
@@ -347,7 +347,7 @@ int nnjit_cached_ranked(int kind, int dtype, int64_t batch, int64_t M, int64_t N
  * (never waited for).  A candidate at least 3% faster than the registered one
  * replaces it; once every candidate has been measured the shape is cached as
  * if nnjit_tune had run.  Calls during stream capture, calls whose operands
- * need the element-load path and calls made while a measurement is still in
+ * are not 16-byte aligned and calls made while a measurement is still in
  * flight are served by the registered configuration without measuring.  With
  * enable = 0 no new measurement starts (shapes in progress keep their
  * registered configuration).  Off by default.  Returns the previous setting. */

@@ -311,6 +311,16 @@ def test_consistent_table_is_generated_from_the_stored_measurement(lib):
         assert any(mb.excluded_by(c, fixed, cfgs) for c in cfgs)
 
 
+def test_config_info_tells_the_columns_of_a_workgroup(lib):
+    """wg_tiles * Nt columns: as many as the LDS stages hold B columns for."""
+    gemm = [c for c in nj.configs() if c["family"].startswith("gemm")]
+    assert all(c["wg_tiles"] == (int(c["name"].rsplit("_n", 1)[1]) if "_n" in c["name"] else 1) for c in gemm)
+    wide = [c for c in gemm if c["wg_tiles"] > 1]
+    assert wide
+    for c in wide:
+        assert c["lds"] == c["stages"] * (c["Mt"] + c["wg_tiles"] * c["Nt"]) * c["Kt"] * 2
+
+
 def test_third_kind_of_staging_is_not_excluded(lib):
     """The fixed settings compare the first two kinds of staging; the third
     (direct=2) is subject to none of them, in either place the rule is written:
