@@ -40,7 +40,8 @@ import workloads  # noqa: E402
 METRIC = "GFLOP/s (%MFMA peak) per GEMM shape; GB/s (%HBM) for GEMV; tune time"
 PEAK_TFLOPS = {"f32": 157.3, "f16": 2516.6}  # dense MFMA peaks of MI355X
 PEAK_HBM_GBS = 8000.0
-RIDGE = {dt: PEAK_TFLOPS[dt] * 1e12 / (PEAK_HBM_GBS * 1e9) for dt in PEAK_TFLOPS}
+# fp32 configurations that take six bf16 products for one (operands split in three bf16 parts)
+SPLIT_PRODUCTS = ("gemm_f32s_", "gemm_f32ws_")
 COLD_BYTES = 1 << 30  # rotate >= 1 GiB of weights per product for bandwidth-bound workloads (MALL is 256 MB)
 HEADLINE = "llama2_7b_prefill512_f32"
 
@@ -120,13 +121,20 @@ def replicas(op, cold: bool) -> int:
     return max(1, math.ceil(COLD_BYTES / op.weight_bytes)) if cold else 1
 
 
-def roofline_of(op, us):
+def mfma_peak(dt, config=""):
+    """TFLOP/s the matrix cores allow a dtype's products in a configuration
+    (its description): for split products a sixth of the dense bf16 rate,
+    which is the fp16 one."""
+    return PEAK_TFLOPS["f16"] / 6 if any("name=" + p in config for p in SPLIT_PRODUCTS) else PEAK_TFLOPS[dt]
+
+
+def roofline_of(op, us, config=""):
     dt = op.dtype
-    ai = op.flops / op.bytes
-    if dt != "q4" and ai >= RIDGE[dt]:   # the 4-bit GEMV runs no MFMA: HBM is its roofline
-        achieved = op.flops / (us * 1e-6) / 1e12
-        return {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS[dt], "unit": "TFLOP/s",
-                "frac": achieved / PEAK_TFLOPS[dt], "traffic": None}
+    # the 4-bit GEMV runs no MFMA: HBM is its roofline
+    if dt != "q4" and op.flops / op.bytes >= mfma_peak(dt, config) * 1e12 / (PEAK_HBM_GBS * 1e9):
+        achieved, peak = op.flops / (us * 1e-6) / 1e12, mfma_peak(dt, config)
+        return {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                "frac": achieved / peak, "traffic": None}
     achieved = op.bytes / (us * 1e-6) / 1e9
     return {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": achieved / PEAK_HBM_GBS, "traffic": None}
@@ -362,20 +370,20 @@ def stream_ceiling_us(nbytes, copies, reps, stream, side):
     return best
 
 
-def per_op_times(runs, reps, ceiling):
+def per_op_times(runs, reps, ceiling, tunes):
     import torch
     stream = torch.cuda.current_stream()
     side = torch.cuda.Stream()
     per_op = []
-    for r in runs:
+    for r, t in zip(runs, tunes):
         us, eus, single = burst_us(lambda i, s, r=r: r.call(i, s), reps, stream, side)
         op = r.op
-        rl = roofline_of(op, us)
+        rl = roofline_of(op, us, t["config"])
         row = {"op": op.name, "shape_MKN": [op.M, op.K, op.N], "batch": op.batch, "dtype": op.dtype,
                "us_per_launch": round(us, 3), "us_per_launch_eager": round(eus, 3),
                "us_single_launch": round(single, 3),
                "gflops": round(op.flops / us / 1e3, 1),
-               "pct_mfma_peak": (round(100 * op.flops / us / 1e6 / PEAK_TFLOPS[op.dtype], 2)
+               "pct_mfma_peak": (round(100 * op.flops / us / 1e6 / mfma_peak(op.dtype, t["config"]), 2)
                                  if op.dtype in PEAK_TFLOPS else None),
                "gbs": round(op.bytes / us / 1e3, 1), "pct_hbm": round(100 * op.bytes / us / 1e3 / PEAK_HBM_GBS, 2),
                "bound": rl["bound"], "pct_roofline": round(100 * rl["frac"], 2)}
@@ -391,10 +399,11 @@ def dominant_roofline(name, runs, per_op, tunes, traffic_db):
     """roofline object of the product with the most time per step."""
     dom = max(range(len(runs)), key=lambda i: per_op[i]["us_per_launch"])
     dop = runs[dom].op
-    rl = roofline_of(dop, per_op[dom]["us_per_launch"])
+    rl = roofline_of(dop, per_op[dom]["us_per_launch"], tunes[dom]["config"])
     cfg_fields = dict(kv.split("=", 1) for kv in nj.nnjit_config_info(tunes[dom]["cfg"]).split() if "=" in kv)
     if cfg_fields["family"].startswith("gemm"):
-        wgs = -(-dop.M // int(cfg_fields["Mt"])) * -(-dop.N // int(cfg_fields["Nt"])) * int(cfg_fields["split"])
+        wgs = -(-dop.M // int(cfg_fields["Mt"])) * -(-dop.N // (int(cfg_fields["Nt"]) * int(cfg_fields["wg_tiles"]))) * int(
+            cfg_fields["split"])
     elif dop.dtype == "q4":
         wgs = -(-dop.N // int(cfg_fields["rows_per_wg"]))
     else:
@@ -418,14 +427,15 @@ def measure(name, args, steps, warmup):
     torch.cuda.synchronize()
     tunes = tune_all(runs)
     st = time_steps(runs, steps, warmup, args.eager)
-    per_op = per_op_times(runs, args.kernel_reps, ceiling=cold and not args.no_stream_ceiling)
+    per_op = per_op_times(runs, args.kernel_reps, cold and not args.no_stream_ceiling, tunes)
     rl = dominant_roofline(name, runs, per_op, tunes, args.traffic_db)
     flops = sum(op.flops for op in ops)
     nbytes = sum(op.bytes for op in ops)
     dt = ops[0].dtype
     out = {"workload": name, "dtype": dt, "value": flops / (st["ms_per_step"] * 1e-3) / 1e9, "unit": "GFLOP/s",
-           "pct_mfma_peak": (round(100 * flops / (st["ms_per_step"] * 1e-3) / 1e12 / PEAK_TFLOPS[dt], 2)
-                             if dt in PEAK_TFLOPS else None),
+           # the time the matrix cores need at the rate of each product's configuration, of the step's
+           "pct_mfma_peak": (round(100 * sum(op.flops / mfma_peak(dt, t["config"]) for op, t in zip(ops, tunes))
+                                   / 1e12 / (st["ms_per_step"] * 1e-3), 2) if dt in PEAK_TFLOPS else None),
            "gbs": round(nbytes / (st["ms_per_step"] * 1e-3) / 1e9, 1), "steps": steps,
            "weight_replicas": max(len(r.Bs) for r in runs), **st,
            "tune": tunes, "tune_ms_max": max(t["tune_ms"] for t in tunes), "per_op": per_op, "roofline": rl,

@@ -35,6 +35,16 @@ def test_roofline_bound_follows_arithmetic_intensity():
     assert bench.roofline_of(q4, 10.0)["bound"] == "hbm"
 
 
+def test_split_products_are_priced_at_the_bf16_rate():
+    """An fp32 product on the bf16 matrix cores takes six of theirs: its
+    fraction is of a sixth of their rate, and stays below one."""
+    head = next(op for op in workloads.workload("llama2_7b_prefill512_f32") if op.N == 32000)
+    for config in ("id=1 family=gemm_f32 name=gemm_f32s_256x256x16_w2x4_p1_vtrue", "name=gemm_f32ws_64x64x16_k4_s4"):
+        r = bench.roofline_of(head, 620.0, config)
+        assert r["bound"] == "mfma" and r["peak"] == pytest.approx(2516.6 / 6) and r["frac"] < 0.6
+    assert bench.roofline_of(head, 947.0, "name=gemm_f32t_128x256x16_w2x4_s4")["peak"] == 157.3
+
+
 def test_measured_traffic_needs_the_exact_config_and_sources(tmp_path):
     nj.load()
     info = "name=gemm_f32w_64x32x16_k4_s4 split=2"
