@@ -445,7 +445,8 @@ gemm_f32w_kernel(GemmParams p)
         lds_char *dst = mine + st * STAGE;
 #pragma unroll
         for (int c = 0; c < NA; ++c) {
-            const bool ok = live && a_ok[c] && a_k[c] + dk < kend;
+            // (SP: rows past M take row 0, as in copy_full: zero sums would be looked into)
+            const bool ok = live && (SP || a_ok[c]) && a_k[c] + dk < kend;
             copy16_to_lds(ok ? a_src[c] + dk : zero, (unsigned)(uintptr_t)(dst + 1024 * c));
         }
 #pragma unroll
@@ -667,6 +668,19 @@ gemm_f32w_kernel(GemmParams p)
                     least = fminf(least, fabsf(acc[i][j][r]));
                 }
             low = low || (least < kTinySum && 32 * j + li < cols);
+        }
+        if (rows < MT && __any(low)) {   // rows past M do not count
+            low = false;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                float least = kTinySum;
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int r = 0; r < I::NR; ++r)
+                        least = fminf(least, 32 * i + 8 * (r >> 2) + 4 * lg + (r & 3) < rows ? fabsf(acc[i][j][r]) : kTinySum);
+                low = low || (least < kTinySum && 32 * j + li < cols);
+            }
         }
         const bool large = __any(top > kTinyMeets);
         const bool open = nmine > 0 && (large || __any(low));

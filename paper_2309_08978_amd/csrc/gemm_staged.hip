@@ -434,6 +434,23 @@ gemm_staged_kernel(GemmParams p)
                 }
             low = low || (least < kTinySum && cwave + 32 * j < cols);
         }
+        // (opaque copies: else the conditions of the stores above are kept in
+        // scalar registers, more than there are)
+        int mrows = rows, mcols = cols;
+        asm volatile("" : "+s"(mrows), "+s"(mcols));
+        if (mrows < MT && __any(low)) {   // rows past M do not count
+            low = false;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                float least = kTinySum;
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        least = fminf(least, rwave + 32 * i + row_of(r) < mrows ? fabsf(acc[i][j][r]) : kTinySum);
+                low = low || (least < kTinySum && cwave + 32 * j < mcols);
+            }
+        }
         const bool open = __syncthreads_or(low || top > kTinyMeets);
         if (open || __any(!(probe == 0.f))) {
             // in LDS: rows of A, groups of 8 columns of B that have a tiny operand;
@@ -468,10 +485,6 @@ gemm_staged_kernel(GemmParams p)
                 }
                 __syncthreads();
             }
-            // (opaque copies: else the conditions of the stores above are kept in
-            // scalar registers, more than there are)
-            int mrows = rows, mcols = cols;
-            asm volatile("" : "+s"(mrows), "+s"(mcols));
             unsigned need[FM][FN], some = 0;   // bit r: sum r is taken anew
 #pragma unroll
             for (int i = 0; i < FM; ++i)

@@ -116,21 +116,21 @@ struct Split8 {
 //   - one below 2^-110 but not zero (tiny): its last bits are below the
 //     smallest bf16 subnormal, 2^-133 (conversion and matrix cores keep
 //     subnormals), and what they lose, up to 2^-134, counts times the other
-//     operand.  If all sums are at least 2^-60 and no operand is above 2^32,
-//     K products lose at most K 2^-101, which the rounding of K fp32 additions
-//     covers; so tiny operands are looked for, with a second pass over the
-//     operands, only where a sum is below 2^-60 or an operand above 2^32.  A sum
-//     of a row of A or column of B that has a tiny one is then taken anew if it
-//     is below 2^-60 or the other matrix has one above 2^32.  Sums of a peaked
-//     softmax's weights times ordinary values thus cost nothing, and zero sums
-//     of zero rows or columns the second pass.
+//     operand.  If no operand is above 2^32, K products lose at most K 2^-101,
+//     half of what the K roundings of an fp32 sum of at least 2^-76 may take;
+//     so tiny operands are looked for, with a second pass over the operands,
+//     only where a sum is below 2^-76 or an operand above 2^32.  A sum of a row
+//     of A or column of B that has a tiny one is then taken anew if it is below
+//     2^-76 or the tile has an operand above 2^32.  Sums of a peaked softmax's
+//     weights times ordinary values thus cost nothing, and zero sums of zero
+//     rows or columns the second pass.
 //
 // The second pass takes the smallest magnitude in as (bits << 1) - 1: zeros wrap
 // to the largest.  (The bits are taken of a scalar: of an element of a vector,
 // __builtin_bit_cast takes those of the first one.)
 constexpr unsigned kTinyStart = 0xffffffffu;
 constexpr unsigned kTinyLimit = (17u << 24) - 1u;   // 2^-110
-constexpr float kTinySum = 0x1p-60f;
+constexpr float kTinySum = 0x1p-76f;
 constexpr float kTinyMeets = 0x1p32f;
 __device__ __forceinline__ unsigned least_of(unsigned least, float x)
 {

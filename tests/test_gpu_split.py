@@ -72,7 +72,8 @@ def _bound(A, B):
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES + [(300, 520, 72)])
-@pytest.mark.parametrize("a,b", [(1e-37, 1e36), (1e-36, 1e30), (1e-34, 1e25), (1e-39, 1e36), (3e-41, 1.0)])
+@pytest.mark.parametrize("a,b", [(1e-37, 1e36), (1e-36, 1e30), (1e-34, 1e25), (1e-39, 1e36), (3e-41, 1.0), (1e-37, 1e14),
+                                 (1e-39, 4e9), (1e-40, 3e17)])
 def test_tiny_operands_that_meet_large_ones(M, N, K, a, b):
     """Tiny operands times large ones, in either order, whole or in one row and
     one column beside ordinary ones: the same bound as above, also where the
@@ -178,3 +179,19 @@ def test_equal_operands(K, value):
     for c in _configs():
         C = _run(c, A, B)
         assert np.all(np.abs(C - R) <= (1 + 6 * -(-K // 16) + 8) * 2.0 ** -24 * R), (c["name"], c["split"])
+
+
+@pytest.mark.parametrize("M,N,K", [(100, 768, 256), (33, 200, 40), (300, 264, 72)])
+def test_rows_past_the_end_are_not_looked_into(M, N, K):
+    """Tiles that reach past M and N: what is read for the rows and columns
+    outside changes no bit of the sums inside, whatever lies in the first row
+    and behind the operands."""
+    rng = np.random.default_rng(18)
+    A = rng.standard_normal((M, K), dtype=np.float32)
+    B = rng.standard_normal((K, N), dtype=np.float32)
+    X = A.copy()
+    X[0] = 0.0
+    for c in _configs():
+        if c["split"] == 1:
+            want, C = _run(c, A, B), _run(c, X, B)
+            assert np.array_equal(C[1:], want[1:]) and not C[0].any(), c["name"]
