@@ -461,22 +461,24 @@ static int split_within(int64_t tiles, int64_t most, int64_t K, int64_t rows) {
 // took scratch before there were row kernels, the smaller ones did not and can
 // be captured without a run before.
 static int predefined_row(const Shape &s, bool aligned, const nnjit_device_limits &d) {
-    static const char *const f16_name[] = {"gemm_f16r_L4_t256_u8", "gemm_f16r_L8_t256_u8", "gemm_f16r_L16_t256_u8",
-                                           "gemm_f16r_L32_t256_u8", "gemm_f16r_L4_t1024_u8"};
-    static const char *const f32_name[] = {"gemm_f32r_L8_t256_u8", "gemm_f32r_L16_t256_u8", "gemm_f32r_L32_t256_u8",
-                                           "gemm_f32r_L64_t256_u8", "gemm_f32r_L8_t1024_u8"};
+    static const int f16_id[] = {id_of("gemm_f16r_L4_t256_u8"), id_of("gemm_f16r_L8_t256_u8"),
+                                 id_of("gemm_f16r_L16_t256_u8"), id_of("gemm_f16r_L32_t256_u8"),
+                                 id_of("gemm_f16r_L4_t1024_u8")};
+    static const int f32_id[] = {id_of("gemm_f32r_L8_t256_u8"), id_of("gemm_f32r_L16_t256_u8"),
+                                 id_of("gemm_f32r_L32_t256_u8"), id_of("gemm_f32r_L64_t256_u8"),
+                                 id_of("gemm_f32r_L8_t1024_u8")};
     const bool f16 = s.dtype == NNJIT_F16;
     const int64_t cus = d.num_cus;
     auto segments = [&](int columns) { return s.batch * ceil_div(s.N, columns); };
     if (aligned && s.K >= (f16 ? 4096 : 2048) && segments(32) <= cus / 2 && segments(64) >= cus / 16)
-        return id_of(f16 ? f16_name[0] : f32_name[0], split_within(segments(32), 4 * cus, s.K, 1));
-    if (f16) return id_of(f16_name[s.K <= 64 ? 3 : s.K <= 128 ? 2 : s.K <= 256 ? 1 : s.K <= 1024 ? 0 : 4]);
+        return id_of(f16 ? "gemm_f16r_L4_t256_u8" : "gemm_f32r_L8_t256_u8", split_within(segments(32), 4 * cus, s.K, 1));
+    if (f16) return f16_id[s.K <= 64 ? 3 : s.K <= 128 ? 2 : s.K <= 256 ? 1 : s.K <= 1024 ? 0 : 4];
     const bool many = segments(256) >= 8 * cus;
     int wide = 0;
     while (!many && wide < 3 && 2 * segments(32 << (wide + 1)) >= 7 * cus) ++wide;
     const int by_sum = s.K <= (many ? 64 : 32) ? 2 : s.K <= 128 ? 1 : 0;
-    if (s.K <= 256 || segments(32) > 2 * cus) return id_of(f32_name[std::max(wide, by_sum)]);
-    return id_of(f32_name[4]);
+    if (s.K <= 256 || segments(32) > 2 * cus) return f32_id[std::max(wide, by_sum)];
+    return f32_id[4];
 }
 
 // All lines below from device times of one MI355X (us; the first of the lite
