@@ -1229,9 +1229,9 @@ constexpr int lds_f32w(int mt, int nt, int ks, int st) {
 
 // The same on the bf16 matrix cores, operands split in three (kcommon.h).  A
 // slab of a 64 x 64 tile takes 24 MFMAs of 32 cycles instead of 32 of 64, and
-// 176 VALU instructions to split that run beside them: 1024 x 1024 x 1024
-// 22.1 -> 18.0 us, 256 x 4096 x 4096 69 -> 54 us, 128 x 2304 x 768 (64 x 32)
-// 10.7 -> 9.9 us.  On 32 x 32 tiles the split costs as much as the MFMAs save
+// 192 VALU instructions to split that run beside them: 1024 x 1024 x 1024
+// 22.1 -> 19 us, 256 x 4096 x 4096 69 -> 57 us, 128 x 2304 x 768 (64 x 32)
+// 10.7 -> 10.0 us.  On 32 x 32 tiles the split costs as much as the MFMAs save
 // (64 x 768 x 768: 7.3 -> 7.6 us), so they are not compiled.
 #define NNJIT_F32WS_VARIANT(MT, NT, KS, ST)                                                                   \
     {"gemm_f32ws_" #MT "x" #NT "x16_k" #KS "_s" #ST, FAM_GEMM_F32, 32, 16, MT, NT, 16, 1, 1, ST, ST - 1, KS, 16, \

@@ -25,10 +25,10 @@
 // SQ_LDS_BANK_CONFLICT is 0.
 //
 // Measured (random operands, one MI355X): 512 x 32000 x 4096, 256 x 256 tiles:
-// 947 -> 637-663 us (142 -> 202-210 TFLOP/s, 1.26 PFLOP/s of bf16 products);
-// 1024 x 4096 x 1024, 128 x 128 tiles: 67 -> 50-52 us; 512 x 4096 x 11008:
-// 335 -> 230 us.  The large tiles run at the power limit: on zero operands the
-// first takes 509 us.  Eight waves beat four (one per SIMD) except where LDS
+// 947 -> 590-640 us (142 -> 210-228 TFLOP/s, 1.26-1.37 PFLOP/s of bf16 products);
+// 1024 x 4096 x 1024, 128 x 128 tiles: 67 -> 49-53 us; 512 x 4096 x 11008:
+// 335 -> 218 us.  The large tiles run at the power limit: on zero operands the
+// first took 509 us (and now pays the second pass, 665).  Eight waves beat four (one per SIMD) except where LDS
 // holds several workgroups.
 //
 // VEC false: operands of any alignment.  gfx950 loads 16 bytes at any element

@@ -790,7 +790,7 @@ int tune(int kind, int dtype, int64_t batch, int64_t M, int64_t N, int64_t K) {
     t_stats.n_lite = (int)lr.ids.size();
     if (lr.ids.empty()) return fail(NNJIT_ENOCFG, "no configuration fits this shape");
     const int limit = std::min<int>((int)lr.ids.size(), kMaxTimed);
-    // the registered kernel this tune competes with: the cached one, else the default
+    // the registered kernel this tune competes with: the cached one, else the first candidate
     const int incumbent = cached >= 0 ? cached : lr.ids[0];
 
     // scratch operands of this exact shape, filled on the device.  A GEMV is
