@@ -6,8 +6,8 @@ or of a ``--pmc`` run (``*_counter_collection.csv``), and prints:
 
 * rocprofv3's own per-kernel statistics (all dispatches of a kernel symbol);
 * per (kernel symbol, grid) statistics over the last ``--last`` dispatches,
-  which is the timed region of bench.py (a kernel instance that serves two
-  shapes is listed once per grid);
+  which are bench.py's bursts of each product by itself, after the timed steps
+  (a kernel instance that serves two shapes is listed once per grid);
 * for a counter run, the per-dispatch mean of each counter per (kernel, grid).
 
     python -m paper_2309_08978_amd.rocprof_summary <rocprofv3 output dir> [--last N]
@@ -63,7 +63,7 @@ def summarize(out_dir: str, last: int, top: int = 12) -> str:
             key = (_short(r["Kernel_Name"]), grid)
             groups.setdefault(key, []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
         lines.append("")
-        lines.append(f"per (kernel, grid) over the last {len(sel)} dispatches (the timed region):")
+        lines.append(f"per (kernel, grid) over the last {len(sel)} dispatches:")
         lines.append(f"  {'kernel':62s} {'WGs':>6s} {'z':>4s} {'n':>5s} {'mean_us':>9s} {'median_us':>9s} {'min_us':>8s}")
         for (k, (gx, gz)), d in sorted(groups.items(), key=lambda kv: -sum(kv[1])):
             lines.append(f"  {k[:62]:62s} {gx:6d} {gz:4d} {len(d):5d} {statistics.mean(d):9.2f} "
